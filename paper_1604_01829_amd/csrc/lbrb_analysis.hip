@@ -13,12 +13,13 @@
 // by the radial position of each origin frame.
 //
 // Series are stored body-major, series[body][frame][k], so the MSD kernels read contiguous
-// frames.  Every sum runs in a fixed order (thread-strided loops, shuffle + LDS trees): the
-// results do not depend on timing.
+// frames.  Every sum runs in a fixed order (thread-strided loops, shuffle + LDS trees) and does
+// not depend on timing, but for the last bits of the binned sums of at most 8 bins.
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include "../../include/lbrb.h"
@@ -66,15 +67,21 @@ __global__ void record_kernel(const Body* bodies, int n_bodies, double* frame)
 
 // ------------------------------------------------------------------ cumulative series
 
-// per-interval increments of one body between frames n-1 and n
-struct LabStep {
-    static constexpr int K = 3;
-    __device__ static void delta(const double* p0, const double* p1, double, double, double d[K])
-    {
-        for (int a = 0; a < 3; ++a) d[a] = p1[a] - p0[a];
-    }
-};
+// the lab-frame displacement: every frame's centre minus the first (no sum: one thread per
+// frame and body, lanes along the frames so that the series is written in order)
+__global__ __launch_bounds__(kBlock) void lab_kernel(const double* __restrict__ traj, int n_frames,
+                                                     int n_bodies, int body0, double* __restrict__ out)
+{
+    const int64_t f = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int b = body0 + blockIdx.y;
+    if (f >= n_frames) return;
+    const double* p0 = traj + 7 * (int64_t)b;
+    const double* p1 = traj + 7 * (f * n_bodies + b);
+    double* o = out + 3 * ((int64_t)b * n_frames + f);
+    for (int a = 0; a < 3; ++a) o[a] = p1[a] - p0[a];
+}
 
+// per-interval increments of one body between frames n-1 and n
 struct BodyStep {
     static constexpr int K = 6;
     // displacement in the body frame at the interval start, and the projection angles
@@ -118,170 +125,401 @@ struct PoreStep {
     }
 };
 
-// One workgroup per body: the F - 1 interval increments are cut into 256 contiguous chunks;
-// each thread sums its chunk, thread 0 turns the chunk sums into prefixes, then each thread
-// writes its chunk's running sums.  out[body][frame][K], 0 at frame 0.
+// The F - 1 interval increments are cut into segments of kSpan, a workgroup each: a thread takes
+// kPer consecutive intervals, a scan over the workgroup (shuffles, then the waves' totals in LDS)
+// gives the sum before them, and the thread writes the segment's running sums.  Then one
+// workgroup per body turns the sums at the segments' ends into totals, and every other value adds
+// the total before its segment.  The sums run in a fixed order.  out[body][frame][K], 0 at frame 0.
+// Bound by the scattered poses (56 of every 56 n_bodies bytes): a segment's are staged in LDS,
+// lanes along the words of a pose.  With one workgroup per body, a serial chunk of the trajectory
+// per thread and each pose waited for in turn, the body-frame series of 32 bodies and 20,000
+// frames took 347 us, this 25 us (three launches); the pore frame 303 and 18 us.
+constexpr int kPer = 2;
+constexpr int kSpan = kBlock * kPer;
+
+// inclusive sums over the workgroup's threads of v[0..K); returns the workgroup's total in `all`
+template <int K>
+__device__ __forceinline__ void block_scan(double v[K], double (*part)[K], double all[K])
+{
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int x = 1; x < 64; x <<= 1)
+        for (int k = 0; k < K; ++k) {
+            const double u = __shfl_up(v[k], x, 64);
+            if (lane >= x) v[k] += u;
+        }
+    if (lane == 63)
+        for (int k = 0; k < K; ++k) part[wave][k] = v[k];
+    __syncthreads();
+    for (int k = 0; k < K; ++k) {
+        double run = 0.0;
+        for (int w = 0; w < kBlock / 64; ++w) {
+            if (w == wave) v[k] += run;
+            run += part[w][k];
+        }
+        all[k] = run;
+    }
+}
+
 template <class Step>
 __global__ __launch_bounds__(kBlock) void cumulate_kernel(const double* __restrict__ traj,
-                                                          int n_frames, int n_bodies, double cx,
-                                                          double cy, double* __restrict__ out,
+                                                          int n_frames, int n_bodies, int n_seg,
+                                                          double cx, double cy,
+                                                          double* __restrict__ out,
                                                           double* __restrict__ radial)
 {
     constexpr int K = Step::K;
-    __shared__ double pre[kBlock][K];
-    const int b = blockIdx.x;
-    const int64_t nint = n_frames - 1;
-    const int64_t chunk = (nint + kBlock - 1) / kBlock;
-    const int64_t i0 = 1 + chunk * threadIdx.x;
-    const int64_t i1 = i0 + chunk < nint + 1 ? i0 + chunk : nint + 1;
-    auto pose = [&](int64_t f) { return traj + 7 * ((int64_t)f * n_bodies + b); };
-    double s[K];
-    for (int k = 0; k < K; ++k) s[k] = 0.0;
-    for (int64_t n = i0; n < i1; ++n) {
-        double d[K];
-        Step::delta(pose(n - 1), pose(n), cx, cy, d);
-        for (int k = 0; k < K; ++k) s[k] += d[k];
-    }
-    for (int k = 0; k < K; ++k) pre[threadIdx.x][k] = s[k];
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double run[K];
-        for (int k = 0; k < K; ++k) run[k] = 0.0;
-        for (int t = 0; t < kBlock; ++t)
-            for (int k = 0; k < K; ++k) {
-                const double v = pre[t][k];
-                pre[t][k] = run[k];
-                run[k] += v;
-            }
+    constexpr int group = 7 * kPer + 1;       // one pad word per thread's frames
+    __shared__ double pose[group * kBlock + 7];
+    __shared__ double part[kBlock / 64][K];
+    const int b = blockIdx.x / n_seg;
+    const int64_t n0 = (int64_t)kSpan * (blockIdx.x % n_seg);
+    for (int e = threadIdx.x; e < 7 * (kSpan + 1); e += kBlock) {
+        // frames n0 ... n0 + kSpan; past the end the last frame stands still
+        const int64_t f = n0 + e / 7 < n_frames ? n0 + e / 7 : n_frames - 1;
+        pose[e + e / (7 * kPer)] = traj[7 * (f * n_bodies + b) + e % 7];
     }
     __syncthreads();
+    auto word = [&](int q, int c) { return pose[group * (threadIdx.x + q / kPer) + 7 * (q % kPer) + c]; };
+    const int64_t n = n0 + kPer * (int64_t)threadIdx.x;
     double* ob = out + (int64_t)b * n_frames * K;
+    double p[kPer + 1][7], d[kPer][K], sum[K], all[K];
+#pragma unroll
+    for (int q = 0; q <= kPer; ++q)
+        for (int c = 0; c < 7; ++c) p[q][c] = word(q, c);
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        Step::delta(p[q], p[q + 1], cx, cy, d[q]);
+        for (int k = 0; k < K; ++k)
+            d[q][k] = (n + q + 1 < n_frames ? d[q][k] : 0.0) + (q > 0 ? d[q > 0 ? q - 1 : 0][k] : 0.0);
+    }
+    for (int k = 0; k < K; ++k) sum[k] = d[kPer - 1][k];
+    block_scan<K>(sum, part, all);
+    // the sum before the thread's intervals: its neighbour's inclusive sum
+    __syncthreads();
+    double* incl = pose;
+    for (int k = 0; k < K; ++k) incl[(threadIdx.x + 1) * K + k] = sum[k];
     if (threadIdx.x == 0)
+        for (int k = 0; k < K; ++k) incl[k] = 0.0;
+    __syncthreads();
+    if (n == 0)
         for (int k = 0; k < K; ++k) ob[k] = 0.0;
-    double run[K];
-    for (int k = 0; k < K; ++k) run[k] = pre[threadIdx.x][k];
-    for (int64_t n = i0; n < i1; ++n) {
-        double d[K];
-        Step::delta(pose(n - 1), pose(n), cx, cy, d);
+#pragma unroll
+    for (int q = 0; q < kPer; ++q)
+        if (n + q + 1 < n_frames)
+            for (int k = 0; k < K; ++k) ob[(n + q + 1) * K + k] = incl[threadIdx.x * K + k] + d[q][k];
+    if (radial)
+#pragma unroll
+        for (int q = 0; q <= kPer; ++q) {     // each thread's frames, and the last frame of all
+            const int64_t f = n + q;
+            if (f < n_frames && (q < kPer || f == n_frames - 1))
+                radial[(int64_t)b * n_frames + f] = hypot(p[q][0] - cx, p[q][1] - cy);
+        }
+}
+
+// the running totals at the segments' ends (frames kSpan, 2 kSpan, ...), one workgroup per body
+template <int K>
+__global__ __launch_bounds__(kBlock) void segment_totals_kernel(double* __restrict__ out, int n_frames,
+                                                                int n_seg)
+{
+    __shared__ double part[2][kBlock / 64][K];
+    double* ob = out + (int64_t)blockIdx.x * n_frames * K;
+    double carry[K];
+    for (int k = 0; k < K; ++k) carry[k] = 0.0;
+    int par = 0;
+    for (int g0 = 0; g0 < n_seg - 1; g0 += kBlock, par ^= 1) {
+        const int g = g0 + threadIdx.x;       // the last segment's end has nothing after it
+        double* end = ob + (int64_t)kSpan * (g + 1) * K;
+        double v[K], all[K];
+        for (int k = 0; k < K; ++k) v[k] = g < n_seg - 1 ? end[k] : 0.0;
+        block_scan<K>(v, part[par], all);
         for (int k = 0; k < K; ++k) {
-            run[k] += d[k];
-            ob[n * K + k] = run[k];
+            if (g < n_seg - 1) end[k] = carry[k] + v[k];
+            carry[k] += all[k];
         }
     }
-    if (radial)
-        for (int64_t f = threadIdx.x; f < n_frames; f += kBlock) {
-            const double* p = pose(f);
-            radial[(int64_t)b * n_frames + f] = hypot(p[0] - cx, p[1] - cy);
-        }
+}
+
+// every value of segments 1 ... but the ends: plus the total before its segment
+template <int K>
+__global__ __launch_bounds__(kBlock) void add_before_kernel(double* __restrict__ out, int n_frames,
+                                                            int n_seg)
+{
+    const int b = blockIdx.x / (n_seg - 1), g = 1 + blockIdx.x % (n_seg - 1);
+    double* ob = out + (int64_t)b * n_frames * K;
+    const double* before = ob + (int64_t)kSpan * g * K;   // frame kSpan g
+    const int64_t first = (int64_t)kSpan * g + 1;
+    const int64_t last = g == n_seg - 1 ? n_frames : first + kSpan - 1;   // the end itself excluded
+    for (int64_t e = first * K + threadIdx.x; e < last * K; e += kBlock) ob[e] += before[e % K];
 }
 
 // ------------------------------------------------------------------ MSDs
 
-// The MSD and rotational MSD kernels: one workgroup per block of kLagBlock consecutive lags
-// and per body.  The origins are staged kChunk at a time in LDS together with the frames
-// the block's lags reach from them, so each frame is read from memory about twice per block
-// instead of twice per (origin, lag).  Thread (l, ph) accumulates lag lag0 + l + 1 over the
-// origins t = ph mod 4 in increasing order; the four phases are then added in a fixed order.
-constexpr int kLagBlock = 64;
-constexpr int kChunk = 256;
-constexpr int kPhases = kBlock / kLagBlock;
-static_assert(kPhases == 4, "four origin phases per lag");
+// The MSD kernels: one workgroup per block of consecutive lags and per body (and component).  A
+// thread takes M consecutive lags by M origins of every chunk of origins; the chunk is staged in
+// LDS with the frames its lags reach, the next chunk's values being in flight to registers.  LG
+// groups of M lags by NT / LG sets of origins.  Every sum runs in a fixed order.
+constexpr int kFillBlocks = 512;   // workgroups of 256 threads that fill the GPU
 
-// stage frames f0 .. f0 + n - 1 of a body-major series (K values per frame) into T; frames
-// at or beyond n_frames read as zero
-template <int K>
-__device__ __forceinline__ void stage(const double* __restrict__ sb, int64_t f0, int n,
-                                      int n_frames, double (*T)[K])
+template <int NT, int LG, int M>
+struct LagShape {
+    static constexpr int threads = NT, groups = LG, tile = M;
+    static constexpr int runs = NT / LG;             // sets of origins
+    static constexpr int chunk = M * runs;           // origins staged at a time
+    static constexpr int lags = M * LG;              // lags of a workgroup
+    static constexpr int reach = chunk + lags;       // frames the chunk's lags reach
+    static constexpr int frames = chunk + reach;
+    static_assert(runs % 32 == 0, "a half-wave shares its lag group");
+};
+
+// The sums of the threads over their lags, added over the sets of origins in a fixed order; the
+// total of lag lag0 + threadIdx.x + 1 is returned to the first S::lags threads.
+template <class S>
+__device__ __forceinline__ double tile_total(double acc[S::tile], double (*part)[S::tile])
 {
-    for (int e = threadIdx.x; e < n * K; e += kBlock) {
-        const int64_t f = f0 + e / K;
-        T[e / K][e % K] = f < n_frames ? sb[f * K + e % K] : 0.0;
+    constexpr int halves = S::runs / 32;              // half-waves per lag group
+#pragma unroll
+    for (int m = 0; m < S::tile; ++m) {
+#pragma unroll
+        for (int x = 16; x >= 1; x >>= 1) acc[m] += __shfl_xor(acc[m], x, 32);
+        if ((threadIdx.x & 31) == 0) part[threadIdx.x >> 5][m] = acc[m];
     }
+    __syncthreads();
+    const int e = threadIdx.x;
+    double v = 0.0;
+    if (e < S::lags)
+        for (int h = 0; h < halves; ++h) v += part[e / S::tile * halves + h][e % S::tile];
+    return v;
 }
 
-// grid (lag block, body): mean over origins of the squared increment of each component
-template <int K>
-__global__ __launch_bounds__(kBlock) void msd_kernel(const double* __restrict__ s, int n_frames,
-                                                     int n_lags, double* __restrict__ out)
+// grid (lag block, body, component): mean over origins of the squared increment.  A thread's
+// origins are consecutive, so the 3 M - 1 = 47 values of its tile feed 256 squared differences
+// from registers: 2 FP64 operations per term against 0.18 LDS reads.  (One lag and one origin at
+// a time, every term read its two values from LDS; 8 x 8 tiles read 0.36 and took 220 us where
+// this takes 198.)  One pad value per M frames spreads the threads' reads over the banks.
+// 128 lags per workgroup where that fills the GPU (64 lags: 227 us, more staging), else 16.
+// 32 bodies, 20,000 frames, 1000 lags: 3 components 569 -> 198 us, 6 components 809 ->
+// 395 us (at the FP64 vector rate: 97 and 195 us).
+using WideMsd = LagShape<256, 8, 16>;
+using NarrowMsd = LagShape<256, 1, 16>;
+
+template <class S>
+__global__ __launch_bounds__(S::threads) __attribute__((amdgpu_waves_per_eu(S::groups > 1 ? 3 : 1)))
+void msd_kernel(const double* __restrict__ s, int n_frames, int n_comp, int n_lags,
+                double* __restrict__ out)
 {
-    __shared__ double A[kChunk][K];                       // origins t0 ..
-    __shared__ double Bt[kChunk + kLagBlock - 1][K];      // frames t0 + lag0 + 1 ..
-    __shared__ double part[kPhases][kLagBlock][K];
-    const int lag0 = blockIdx.x * kLagBlock, b = blockIdx.y;
-    const int l = threadIdx.x % kLagBlock, ph = threadIdx.x / kLagBlock;
-    const int tau = lag0 + l + 1;
-    const double* sb = s + (int64_t)b * n_frames * K;
-    double acc[K];
-    for (int k = 0; k < K; ++k) acc[k] = 0.0;
-    for (int64_t t0 = 0; t0 + lag0 + 1 < n_frames; t0 += kChunk) {
-        __syncthreads();
-        stage<K>(sb, t0, kChunk, n_frames, A);
-        stage<K>(sb, t0 + lag0 + 1, kChunk + kLagBlock - 1, n_frames, Bt);
-        __syncthreads();
-        // origins t0 + o with t0 + o + tau < n_frames; a counted loop, unrolled, lets the
-        // LDS reads of several origins be in flight together
-        const int o_end = (int)min<int64_t>(kChunk, n_frames - tau - t0);
-#pragma unroll 8
-        for (int o = ph; o < o_end; o += kPhases)
-            for (int k = 0; k < K; ++k) {
-                const double d = Bt[o + l][k] - A[o][k];
-                acc[k] += d * d;
-            }
-    }
-    for (int k = 0; k < K; ++k) part[ph][l][k] = acc[k];
-    __syncthreads();
-    if (ph == 0 && tau <= n_lags)
-        for (int k = 0; k < K; ++k) {
-            const double v = (part[0][l][k] + part[1][l][k]) + (part[2][l][k] + part[3][l][k]);
-            out[((int64_t)b * n_lags + tau - 1) * K + k] = v / (double)(n_frames - tau);
+    constexpr int NT = S::threads, M = S::tile;
+    __shared__ double A[S::chunk / M * (M + 1)];           // origins t0 ..
+    __shared__ double Bt[S::reach / M * (M + 1)];          // frames t0 + lag0 + 1 ..
+    __shared__ double part[NT / 32][M];
+    const int lag0 = blockIdx.x * S::lags, b = blockIdx.y, comp = blockIdx.z;
+    const int r = threadIdx.x % S::runs, lg = threadIdx.x / S::runs;
+    const double* sb = s + (int64_t)b * n_frames * n_comp + comp;
+    constexpr int NA = S::chunk / NT, NB = (S::reach + NT - 1) / NT;
+    double na[NA], nb[NB];
+    auto load = [&](int64_t t0) {                          // frames past the end: zero
+        const double* pa = sb + t0 * n_comp;
+        const double* pb = pa + (int64_t)(lag0 + 1) * n_comp;
+        const int64_t left = n_frames - t0;
+#pragma unroll
+        for (int q = 0; q < NA; ++q) {
+            const int e = threadIdx.x + q * NT;
+            na[q] = e < left ? pa[(int64_t)e * n_comp] : 0.0;
         }
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+            const int e = threadIdx.x + q * NT;
+            nb[q] = e < left - lag0 - 1 ? pb[(int64_t)e * n_comp] : 0.0;
+        }
+    };
+    double acc[M];
+#pragma unroll
+    for (int m = 0; m < M; ++m) acc[m] = 0.0;
+    const double* a = A + (M + 1) * r;
+    const double* w = Bt + (M + 1) * (r + lg);
+    load(0);
+    for (int64_t t0 = 0; t0 + lag0 + 1 < n_frames; t0 += S::chunk) {
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < NA; ++q) {
+            const int e = threadIdx.x + q * NT;
+            A[e + e / M] = na[q];
+        }
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+            const int e = threadIdx.x + q * NT;
+            if (e < S::reach) Bt[e + e / M] = nb[q];
+        }
+        __syncthreads();
+        load(t0 + S::chunk);
+        // frames from the tile's first (origin, lag) on
+        const int64_t left = n_frames - (t0 + M * r + lag0 + M * lg + 1);
+        if (left >= 2 * M - 1) {                            // every origin reaches every lag
+            double y[2 * M - 1];
+#pragma unroll
+            for (int j = 0; j < 2 * M - 1; ++j) y[j] = w[j + j / M];
+#pragma unroll
+            for (int i = 0; i < M; ++i) {
+                const double x = a[i];
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    const double d = y[i + m] - x;
+                    acc[m] += d * d;
+                }
+            }
+        } else if (left > 0) {
+#pragma unroll 1
+            for (int i = 0; i < M; ++i)
+#pragma unroll
+                for (int m = 0; m < M; ++m)
+                    if (i + m < left) {
+                        const double d = w[i + m + (i + m) / M] - a[i];
+                        acc[m] += d * d;
+                    }
+        }
+    }
+    const double v = tile_total<S>(acc, part);
+    const int tau = lag0 + (int)threadIdx.x + 1;
+    if ((int)threadIdx.x < S::lags && tau <= n_lags)
+        out[((int64_t)b * n_lags + tau - 1) * n_comp + comp] = v / (double)(n_frames - tau);
+}
+
+// theta^2 / (1 - cos theta) as a polynomial in y = 1 - cos theta on [0, 1]: interpolated at the
+// Chebyshev nodes from the series theta^2 = 2 sum_n (2 y)^n / (n^2 C(2n, n)) (that of the squared
+// arcsine of sqrt(y / 2)); relative error below 2e-17
+__device__ __forceinline__ double angle_poly(double y)
+{
+    constexpr double c[20] = {0x1.0000000000000p+1, 0x1.55555555555f8p-2, 0x1.6c16c16c01aadp-4, 0x1.d41d41e56b008p-6,
+                               0x1.4ce19727a237cp-7, 0x1.f85e9253c495cp-9, 0x1.8ef8d0e792e25p-10, 0x1.47423977630aap-11,
+                               0x1.010ddcd930bd4p-12, 0x1.6dfbf751fe7a6p-13, -0x1.4e0a7b21d29e3p-13, 0x1.1ade30efbb8f1p-11,
+                               -0x1.03fce21011ae4p-10, 0x1.879e9e385f6dfp-10, -0x1.bbbdc34bad526p-10, 0x1.7bf11ffa6ad20p-10,
+                               -0x1.d8e9353bd632ep-11, 0x1.9717eb8ade077p-12, -0x1.b20de0c460ec2p-14, 0x1.b875556a46750p-17};
+    double v = c[20 - 1];
+#pragma unroll
+    for (int n = 20 - 2; n >= 0; --n) v = fma(v, y, c[n]);
+    return v;
+}
+
+// cos(theta / 2) = sqrt(1 - d / 2), d = 1 - cos theta in [0, 2]: the hardware's reciprocal square
+// root, two coupled Newton steps and a correction by the remainder (within an ulp)
+__device__ __forceinline__ double half_cosine(double d)
+{
+    const double x = fmax(fma(-0.5, d, 1.0), 1e-300);
+    const double r = __builtin_amdgcn_rsq(x);
+    double g = x * r, h = 0.5 * r;
+    double e = fma(-h, g, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+    e = fma(-h, g, 0.5);
+    g = fma(g, e, g);
+    return fma(fma(-g, g, x), h, g);
 }
 
 // grid (lag block, body): mean over origins of the squared angle between the reference
-// vectors; the unit vectors R(q) r / |R(q) r| are computed once per staged frame
-__global__ __launch_bounds__(kBlock) void rotation_msd_kernel(const double* __restrict__ traj,
-                                                              int n_frames, int n_bodies,
-                                                              const double* __restrict__ ref,
-                                                              int n_lags, double* __restrict__ out)
+// vectors.  The unit vectors R(q) r / |R(q) r| are computed once per staged frame; a thread's
+// origins are NT / LG apart, so that the lanes' reads are consecutive.  The squared angle is
+// analytic in the cosine at theta = 0, so it is a polynomial in 1 - cos theta up to a right
+// angle, and beyond from the half angle: with an arccosine and its square root per term 32
+// bodies, 20,000 frames and 1000 lags took 2135 us, this 1040 us.  A chunk with a
+// non-finite vector takes the arccosine itself, so that it propagates as before.  128 lags
+// per workgroup where that fills the GPU (64 at twice the wavefronts: 1130 us), else 16.
+using WideAngles = LagShape<512, 16, 8>;
+using NarrowAngles = LagShape<256, 2, 8>;
+
+template <class S>
+__global__ __launch_bounds__(S::threads) __attribute__((amdgpu_waves_per_eu(2)))
+void rotation_msd_kernel(const double* __restrict__ traj, int n_frames, int n_bodies,
+                         const double* __restrict__ ref, int n_lags, double* __restrict__ out)
 {
-    __shared__ double A[kChunk][3];
-    __shared__ double Bt[kChunk + kLagBlock - 1][3];
-    __shared__ double part[kPhases][kLagBlock];
-    const int lag0 = blockIdx.x * kLagBlock, b = blockIdx.y;
-    const int l = threadIdx.x % kLagBlock, ph = threadIdx.x / kLagBlock;
-    const int tau = lag0 + l + 1;
-    const double r[3] = {ref[3 * b], ref[3 * b + 1], ref[3 * b + 2]};
-    auto unit = [&](int64_t f, double* p) {
-        if (f >= n_frames) { p[0] = p[1] = p[2] = 0.0; return; }
-        double R[9];
-        rot_of(traj + 7 * (f * n_bodies + b) + 3, R);
-        for (int a = 0; a < 3; ++a) p[a] = R[3 * a] * r[0] + R[3 * a + 1] * r[1] + R[3 * a + 2] * r[2];
-        const double n = sqrt(p[0] * p[0] + p[1] * p[1] + p[2] * p[2]);
-        for (int a = 0; a < 3; ++a) p[a] /= n;
+    constexpr int NT = S::threads, M = S::tile;
+    __shared__ double A[S::chunk][3];                      // origins t0 ..
+    __shared__ double Bt[S::reach][3];                     // frames t0 + lag0 + 1 ..
+    __shared__ double part[NT / 32][M];
+    const int lag0 = blockIdx.x * S::lags, b = blockIdx.y;
+    const int r = threadIdx.x % S::runs, lg = threadIdx.x / S::runs;
+    const double rv[3] = {ref[3 * b], ref[3 * b + 1], ref[3 * b + 2]};
+    constexpr int NF = (S::frames + NT - 1) / NT;
+    double q[NF][4];
+    // staged frame e: origin t0 + e, or frame t0 + lag0 + 1 + (e - chunk)
+    auto frame = [&](int64_t t0, int e) { return e < S::chunk ? t0 + e : t0 + lag0 + 1 + (e - S::chunk); };
+    auto load = [&](int64_t t0) {
+#pragma unroll
+        for (int n = 0; n < NF; ++n) {
+            const int e = threadIdx.x + n * NT;
+            const int64_t f = frame(t0, e);
+            for (int c = 0; c < 4; ++c)
+                q[n][c] = e < S::frames && f < n_frames ? traj[7 * (f * n_bodies + b) + 3 + c] : 0.0;
+        }
     };
-    double acc = 0.0;
-    for (int64_t t0 = 0; t0 + lag0 + 1 < n_frames; t0 += kChunk) {
+    double acc[M];
+#pragma unroll
+    for (int m = 0; m < M; ++m) acc[m] = 0.0;
+    load(0);
+    for (int64_t t0 = 0; t0 + lag0 + 1 < n_frames; t0 += S::chunk) {
+        bool bad = false;
         __syncthreads();
-        for (int e = threadIdx.x; e < kChunk; e += kBlock) unit(t0 + e, A[e]);
-        for (int e = threadIdx.x; e < kChunk + kLagBlock - 1; e += kBlock)
-            unit(t0 + lag0 + 1 + e, Bt[e]);
-        __syncthreads();
-        const int o_end = (int)min<int64_t>(kChunk, n_frames - tau - t0);
-#pragma unroll 8
-        for (int o = ph; o < o_end; o += kPhases) {
-            const double* p0 = A[o];
-            const double* p1 = Bt[o + l];
-            double c = p0[0] * p1[0] + p0[1] * p1[1] + p0[2] * p1[2];
-            c = c > 1.0 ? 1.0 : (c < -1.0 ? -1.0 : c);
-            const double th = acos(c);
-            acc += th * th;
+#pragma unroll
+        for (int n = 0; n < NF; ++n) {
+            const int e = threadIdx.x + n * NT;
+            if (e >= S::frames) continue;
+            double p[3] = {0.0, 0.0, 0.0};
+            if (frame(t0, e) < n_frames) {
+                double R[9];
+                rot_of(q[n], R);
+                for (int c = 0; c < 3; ++c)
+                    p[c] = R[3 * c] * rv[0] + R[3 * c + 1] * rv[1] + R[3 * c + 2] * rv[2];
+                const double len = sqrt(p[0] * p[0] + p[1] * p[1] + p[2] * p[2]);
+                for (int c = 0; c < 3; ++c) p[c] /= len;
+            }
+            bad = bad || !(fabs(p[0]) + fabs(p[1]) + fabs(p[2]) < 4.0);
+            double* to = e < S::chunk ? A[e] : Bt[e - S::chunk];
+            for (int c = 0; c < 3; ++c) to[c] = p[c];
+        }
+        bad = __syncthreads_or(bad) != 0;
+        load(t0 + S::chunk);
+        const bool whole = !bad && t0 + S::chunk + lag0 + S::lags <= n_frames;
+#pragma unroll 1
+        for (int i = 0; i < M; ++i) {
+            const int o = r + S::runs * i;
+            const double x0 = A[o][0], x1 = A[o][1], x2 = A[o][2];
+            const double (*y)[3] = Bt + o + M * lg;
+            double d[M];
+#pragma unroll
+            for (int m = 0; m < M; ++m) d[m] = x0 * y[m][0] + x1 * y[m][1] + x2 * y[m][2];
+            if (whole) {
+                bool wide = false;
+#pragma unroll
+                for (int m = 0; m < M; ++m) {
+                    d[m] = fmin(fmax(1.0 - d[m], 0.0), 2.0);
+                    wide = wide || d[m] > 1.0;
+                }
+                if (__any(wide)) {
+#pragma unroll
+                    for (int m = 0; m < M; ++m) {
+                        const bool far = d[m] > 1.0;
+                        const double z = far ? 1.0 - half_cosine(d[m]) : d[m];
+                        acc[m] += (far ? 4.0 : 1.0) * z * angle_poly(z);
+                    }
+                } else {
+#pragma unroll
+                    for (int m = 0; m < M; ++m) acc[m] += d[m] * angle_poly(d[m]);
+                }
+            } else {
+                const int64_t t = t0 + o + lag0 + M * lg + 1;
+#pragma unroll
+                for (int m = 0; m < M; ++m)
+                    if (t + m < n_frames) {
+                        const double c = d[m] > 1.0 ? 1.0 : (d[m] < -1.0 ? -1.0 : d[m]);
+                        const double th = acos(c);
+                        acc[m] += th * th;
+                    }
+            }
         }
     }
-    part[ph][l] = acc;
-    __syncthreads();
-    if (ph == 0 && tau <= n_lags)
-        out[(int64_t)b * n_lags + tau - 1] =
-            ((part[0][l] + part[1][l]) + (part[2][l] + part[3][l])) / (double)(n_frames - tau);
+    const double v = tile_total<S>(acc, part);
+    const int tau = lag0 + (int)threadIdx.x + 1;
+    if ((int)threadIdx.x < S::lags && tau <= n_lags)
+        out[(int64_t)b * n_lags + tau - 1] = v / (double)(n_frames - tau);
 }
 
 // grid (lag, bin), for more than kTileBins bins: sums of the squared increments from the
@@ -321,81 +559,217 @@ __global__ __launch_bounds__(kBlock) void binned_msd_kernel(const double* __rest
     }
 }
 
-// grid (lag block, body), for at most kTileBins bins: the MSD kernel's staging, with each
-// staged origin's bin found once.  The lanes of a wave share their origin (they differ in the
-// lag), so the bin is uniform across the wave and only its own sums are updated.  Thread
-// (l, ph) keeps every bin's sums for lag lag0 + l + 1 in registers; the four phases are added
-// in a fixed order and each body's sums are added to the outputs with device atomics, so the
-// order in which bodies are added (and the last bits of the sums) is not fixed; the counts
-// are whole numbers and exact.
+// For at most kTileBins bins: grid (lag block, body, segment of origins).  A lane takes ML
+// consecutive lags and walks the origins of its wave's share of a chunk in order, so its ML
+// frames slide along (one new LDS value per origin and component, 2 ML FP64 operations) and the
+// origin is the same for the whole wave: its frame comes by scalar loads, and its bin is
+// uniform.  The running sums stay in registers while the bin does (a body crosses bin edges
+// rarely) and are added to the workgroup's LDS sums of that bin when it changes.  The reached
+// frames are staged by their index modulo ML so that the lanes' reads are consecutive.  The sums
+// of bodies and segments are added to the outputs with device atomics, so their order (and the
+// last bits of the sums) is not fixed; the counts are whole numbers and exact.  Segments: enough
+// workgroups to fill the GPU.
+// 32 bodies, 20,000 frames, 1000 lags, 8 bins: 1219 -> 300 us (one lag per lane: every
+// term read its frames from LDS and branched on its bin).
 constexpr int kTileBins = 8;
+constexpr int kBinBlock = 512;
+constexpr int kBinChunk = kBinBlock;             // origins staged at a time: 64 per wave
+constexpr int kGroup = 4;                        // origins between looks at their bins
 
-template <int K>
-__global__ __launch_bounds__(kBlock) void binned_msd_tiled_kernel(
+template <int K, int ML>
+__global__ __launch_bounds__(kBinBlock) __attribute__((amdgpu_waves_per_eu(4)))
+void binned_msd_tiled_kernel(
     const double* __restrict__ s, const double* __restrict__ radial, int n_frames,
-    const double* __restrict__ edges, int n_bins, int n_lags, double* __restrict__ sums,
-    double* __restrict__ counts)
+    const double* __restrict__ edges, int n_bins, int n_lags, int64_t segment,
+    double* __restrict__ sums, double* __restrict__ counts)
 {
-    __shared__ double A[kChunk][K];
-    __shared__ double Bt[kChunk + kLagBlock - 1][K];
-    __shared__ int bin_of[kChunk];
-    __shared__ double part[kPhases][kLagBlock];
-    const int lag0 = blockIdx.x * kLagBlock, b = blockIdx.y;
-    const int l = threadIdx.x % kLagBlock, ph = threadIdx.x / kLagBlock;
-    const int tau = lag0 + l + 1;
-    const double* sb = s + (int64_t)b * n_frames * K;
-    const double* rb = radial + (int64_t)b * n_frames;
-    double acc[kTileBins][K + 1];
+    constexpr int lags = 64 * ML;
+    constexpr int reach = kBinChunk + lags + ML;
+    __shared__ double Bt[K][ML][reach / ML];
+    __shared__ double total[kTileBins][ML][K][64];
+    __shared__ int count[kTileBins][ML][64];    // of the origins that not every lag reaches
+    __shared__ int full[kTileBins];             // of the others
+    const int lag0 = blockIdx.x * lags, b = blockIdx.y;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const double* __restrict__ sb = s + (int64_t)b * n_frames * K;
+    const double* __restrict__ rb = radial + (int64_t)b * n_frames;
+    for (int e = threadIdx.x; e < kTileBins * ML * K * 64; e += kBinBlock) (&total[0][0][0][0])[e] = 0.0;
+    for (int e = threadIdx.x; e < kTileBins * ML * 64; e += kBinBlock) (&count[0][0][0])[e] = 0;
+    if (threadIdx.x < kTileBins) full[threadIdx.x] = 0;
+    double acc[ML][K];
 #pragma unroll
-    for (int q = 0; q < kTileBins; ++q)
-        for (int k = 0; k <= K; ++k) acc[q][k] = 0.0;
-    for (int64_t t0 = 0; t0 + lag0 + 1 < n_frames; t0 += kChunk) {
+    for (int m = 0; m < ML; ++m)
+        for (int k = 0; k < K; ++k) acc[m][k] = 0.0;
+    int cur = -1;                               // the bin of acc (-1: none, dropped)
+    auto flush = [&]() {
+        if (cur >= 0) {
+#pragma unroll
+            for (int m = 0; m < ML; ++m)
+                for (int k = 0; k < K; ++k) atomicAdd(&total[cur][m][k][lane], acc[m][k]);
+        }
+#pragma unroll
+        for (int m = 0; m < ML; ++m)
+            for (int k = 0; k < K; ++k) acc[m][k] = 0.0;
+    };
+    const int64_t begin = segment * blockIdx.z;
+    const int64_t end = begin + segment < n_frames ? begin + segment : n_frames;
+    for (int64_t t0 = begin; t0 < end && t0 + lag0 + 1 < n_frames; t0 += kBinChunk) {
         __syncthreads();
-        stage<K>(sb, t0, kChunk, n_frames, A);
-        stage<K>(sb, t0 + lag0 + 1, kChunk + kLagBlock - 1, n_frames, Bt);
-        for (int e = threadIdx.x; e < kChunk; e += kBlock) {
-            int j = -1;
-            if (t0 + e < n_frames) {
-                const double r = rb[t0 + e];
-                for (int q = 0; q < n_bins; ++q)
-                    if (r >= edges[q] && r < edges[q + 1]) j = q;
-            }
-            bin_of[e] = j;
+        for (int e = threadIdx.x; e < reach * K; e += kBinBlock) {
+            const int64_t f = t0 + lag0 + 1 + e / K;
+            Bt[e % K][e / K % ML][e / K / ML] = f < n_frames ? sb[f * K + e % K] : 0.0;
         }
         __syncthreads();
-        const int o_end = (int)min<int64_t>(kChunk, n_frames - tau - t0);
-#pragma unroll 2
-        for (int o = ph; o < o_end; o += kPhases) {
-            const int j = __builtin_amdgcn_readfirstlane(bin_of[o]);   // uniform in the wave
-            if (j < 0) continue;
-            double d2[K];
+        // the bin of each of the wave's 64 origins, one per lane (-1: none)
+        const int64_t tw = t0 + 64 * wave;
+        int bin = -1;
+        if (tw + lane < end) {
+            const double rad = rb[tw + lane];
+            for (int q = 0; q < n_bins; ++q)
+                if (rad >= edges[q] && rad < edges[q + 1]) bin = q;
+        }
+        // whether every origin reaches every lag: then an origin counts once for all of them
+        const bool whole = tw + 64 <= end && tw + 63 + lag0 + lags < n_frames;
+        if (whole)
+            for (int q = 0; q < n_bins; ++q) {
+                const int c = __popcll(__ballot(bin == q));
+                if (c > 0 && lane == 0) atomicAdd(&full[q], c);
+            }
+        double w[ML][K];                        // the frames of the lane's lags
+#pragma unroll
+        for (int m = 0; m < ML; ++m)
+            for (int k = 0; k < K; ++k) w[m][k] = Bt[k][m][64 / ML * wave + lane];
+        // one origin, its frame in a: the lane's lags, then the window moves on
+        auto slide = [&](int o, int i) {
+#pragma unroll
             for (int k = 0; k < K; ++k) {
-                const double d = Bt[o + l][k] - A[o][k];
-                d2[k] = d * d;
-            }
 #pragma unroll
-            for (int q = 0; q < kTileBins; ++q)
-                if (q == j) {
-                    for (int k = 0; k < K; ++k) acc[q][k] += d2[k];
-                    acc[q][K] += 1.0;
+                for (int m = 0; m + 1 < ML; ++m) w[m][k] = w[m + 1][k];
+                w[ML - 1][k] = Bt[k][i % ML][64 / ML * wave + o / ML + 1 + lane];
+            }
+        };
+        auto add = [&](const double a[K]) {
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+#pragma unroll
+                for (int m = 0; m < ML; ++m) {
+                    const double d = w[m][k] - a[k];
+                    acc[m][k] += d * d;
                 }
-        }
-    }
+        };
+        if (whole) {
+            // the frames of a group of origins, loaded one group ahead
+            double a[kGroup][K], next[kGroup][K];
+            auto fetch = [&](int g) {
 #pragma unroll
-    for (int q = 0; q < kTileBins; ++q) {
-        if (q >= n_bins) break;
-        for (int k = 0; k <= K; ++k) {
-            __syncthreads();
-            part[ph][l] = acc[q][k];
-            __syncthreads();
-            if (ph == 0 && tau <= n_lags) {
-                const double v = (part[0][l] + part[1][l]) + (part[2][l] + part[3][l]);
-                const int64_t o = (int64_t)q * n_lags + tau - 1;
-                if (k < K) atomicAdd(sums + o * K + k, v);
-                else atomicAdd(counts + o, v);
+                for (int i = 0; i < kGroup; ++i)
+                    for (int k = 0; k < K; ++k) next[i][k] = sb[(tw + g + i) * K + k];   // uniform
+            };
+            fetch(0);
+#pragma unroll 1
+            for (int g = 0; g < 64; g += kGroup) {
+#pragma unroll
+                for (int i = 0; i < kGroup; ++i)
+                    for (int k = 0; k < K; ++k) a[i][k] = next[i][k];
+                fetch(g + kGroup < 64 ? g + kGroup : 0);
+                constexpr unsigned long long group = (1ull << kGroup) - 1;
+                if (((__ballot(bin == cur) >> g) & group) == group) {
+#pragma unroll
+                    for (int i = 0; i < kGroup; ++i) {
+                        add(a[i]);
+                        slide(g + i, i);
+                    }
+                } else {
+#pragma unroll
+                    for (int i = 0; i < kGroup; ++i) {
+                        const int j = __builtin_amdgcn_readlane(bin, g + i);
+                        if (j != cur) {
+                            flush();
+                            cur = j;
+                        }
+                        add(a[i]);
+                        slide(g + i, i);
+                    }
+                }
+            }
+            continue;
+        }
+        // origins that not every lag reaches, or fewer than a wave's share
+        flush();
+        cur = -1;
+#pragma unroll 1
+        for (int g = 0; g < 64; g += ML) {
+            if (tw + g >= end || tw + g + lag0 + 1 >= n_frames) break;     // uniform
+#pragma unroll
+            for (int i = 0; i < ML; ++i) {
+                const int j = __builtin_amdgcn_readlane(bin, g + i);
+                const int64_t left = n_frames - 1 - (tw + g + i) - lag0 - ML * lane;
+                // (a scalar load may run for a wave whose lanes are all done: stay in bounds)
+                const int64_t t = tw + g + i < n_frames ? tw + g + i : n_frames - 1;
+                if (j >= 0) {
+#pragma unroll
+                    for (int m = 0; m < ML; ++m)
+                        if (m < left) {
+                            for (int k = 0; k < K; ++k) {
+                                const double d = w[m][k] - sb[t * K + k];
+                                atomicAdd(&total[j][m][k][lane], d * d);
+                            }
+                            atomicAdd(&count[j][m][lane], 1);
+                        }
+                }
+                slide(g + i, i);
             }
         }
     }
+    flush();
+    __syncthreads();
+    for (int e = threadIdx.x; e < n_bins * lags * (K + 1); e += kBinBlock) {
+        const int k = e % (K + 1), m = e / (K + 1) % lags, q = e / (K + 1) / lags;
+        if (lag0 + m >= n_lags) continue;
+        const int64_t o = (int64_t)q * n_lags + lag0 + m;
+        if (k < K) atomicAdd(sums + o * K + k, total[q][m % ML][k][m / ML]);
+        else atomicAdd(counts + o, (double)(full[q] + count[q][m % ML][m / ML]));
+    }
+}
+
+// zero sums[0..n) and counts[0..m) (a kernel: a captured memset has given wrong replays)
+__global__ void zero_sums_kernel(double* sums, int64_t n, double* counts, int64_t m)
+{
+    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (i < n) sums[i] = 0.0;
+    else if (i < n + m) counts[i - n] = 0.0;
+}
+
+template <class Step>
+void launch_cumulate(const double* traj, int32_t n_frames, int32_t n_bodies, double cx, double cy,
+                     double* out, double* radial, hipStream_t s)
+{
+    const int n_seg = std::max<int>(1, (int)(((int64_t)n_frames - 1 + kSpan - 1) / kSpan));
+    hipLaunchKernelGGL((cumulate_kernel<Step>), dim3((unsigned)n_bodies * n_seg), dim3(kBlock), 0, s,
+                       traj, n_frames, n_bodies, n_seg, cx, cy, out, radial);
+    if (n_seg == 1) return;
+    hipLaunchKernelGGL((segment_totals_kernel<Step::K>), dim3(n_bodies), dim3(kBlock), 0, s, out,
+                       n_frames, n_seg);
+    hipLaunchKernelGGL((add_before_kernel<Step::K>), dim3((unsigned)n_bodies * (n_seg - 1)),
+                       dim3(kBlock), 0, s, out, n_frames, n_seg);
+}
+
+template <class S>
+int64_t lag_blocks(int32_t n_lags) { return (n_lags + S::lags - 1) / S::lags; }
+
+template <int K, int ML>
+void launch_binned(const double* series, const double* radial, int32_t n_frames, int32_t n_bodies,
+                   const double* edges, int32_t n_bins, int32_t n_lags, double* sums,
+                   double* counts, hipStream_t s)
+{
+    // segments of origins: at least one chunk each, and no more workgroups than fill the GPU
+    const int64_t blocks = (n_lags + 64 * ML - 1) / (64 * ML);
+    const int64_t chunks = (n_frames + kBinChunk - 1) / kBinChunk;
+    const int64_t per = std::max<int64_t>(1, chunks * blocks * n_bodies / kFillBlocks);
+    const dim3 grid((unsigned)blocks, n_bodies, (unsigned)((chunks + per - 1) / per));
+    hipLaunchKernelGGL((binned_msd_tiled_kernel<K, ML>), grid, dim3(kBinBlock), 0, s, series, radial,
+                       n_frames, edges, n_bins, n_lags, per * kBinChunk, sums, counts);
 }
 
 bool frames_ok(const double* p, int32_t n_frames, int32_t n_bodies)
@@ -424,8 +798,9 @@ int lb_traj_lab_frame(const double* traj, int32_t n_frames, int32_t n_bodies, do
                         void* stream)
 {
     if (!frames_ok(traj, n_frames, n_bodies) || !out) return LB_ERR_ARG;
-    hipLaunchKernelGGL((cumulate_kernel<LabStep>), dim3(n_bodies), dim3(kBlock), 0,
-                       (hipStream_t)stream, traj, n_frames, n_bodies, 0.0, 0.0, out, nullptr);
+    for (int32_t b = 0; b < n_bodies; b += 65535)   // (bodies along the grid's second dimension)
+        hipLaunchKernelGGL(lab_kernel, dim3((n_frames + kBlock - 1) / kBlock, std::min(n_bodies - b, 65535)),
+                           dim3(kBlock), 0, (hipStream_t)stream, traj, n_frames, n_bodies, b, out);
     return launched();
 }
 
@@ -433,8 +808,7 @@ int lb_traj_body_frame(const double* traj, int32_t n_frames, int32_t n_bodies, d
                          void* stream)
 {
     if (!frames_ok(traj, n_frames, n_bodies) || !out) return LB_ERR_ARG;
-    hipLaunchKernelGGL((cumulate_kernel<BodyStep>), dim3(n_bodies), dim3(kBlock), 0,
-                       (hipStream_t)stream, traj, n_frames, n_bodies, 0.0, 0.0, out, nullptr);
+    launch_cumulate<BodyStep>(traj, n_frames, n_bodies, 0.0, 0.0, out, nullptr, (hipStream_t)stream);
     return launched();
 }
 
@@ -444,8 +818,7 @@ int lb_traj_pore_frame(const double* traj, int32_t n_frames, int32_t n_bodies, d
     if (!frames_ok(traj, n_frames, n_bodies) || !out || !radial || !std::isfinite(cx) ||
         !std::isfinite(cy))
         return LB_ERR_ARG;
-    hipLaunchKernelGGL((cumulate_kernel<PoreStep>), dim3(n_bodies), dim3(kBlock), 0,
-                       (hipStream_t)stream, traj, n_frames, n_bodies, cx, cy, out, radial);
+    launch_cumulate<PoreStep>(traj, n_frames, n_bodies, cx, cy, out, radial, (hipStream_t)stream);
     return launched();
 }
 
@@ -455,16 +828,14 @@ int lb_traj_msd(const double* series, int32_t n_frames, int32_t n_bodies, int32_
     if (!frames_ok(series, n_frames, n_bodies) || !out || k < 1 || k > 6 || n_lags < 1 ||
         n_lags >= n_frames || n_bodies > 65535)
         return LB_ERR_ARG;
-    const dim3 grid((n_lags + kLagBlock - 1) / kLagBlock, n_bodies);
-    hipStream_t s = (hipStream_t)stream;
-    switch (k) {
-    case 1: hipLaunchKernelGGL((msd_kernel<1>), grid, dim3(kBlock), 0, s, series, n_frames, n_lags, out); break;
-    case 2: hipLaunchKernelGGL((msd_kernel<2>), grid, dim3(kBlock), 0, s, series, n_frames, n_lags, out); break;
-    case 3: hipLaunchKernelGGL((msd_kernel<3>), grid, dim3(kBlock), 0, s, series, n_frames, n_lags, out); break;
-    case 4: hipLaunchKernelGGL((msd_kernel<4>), grid, dim3(kBlock), 0, s, series, n_frames, n_lags, out); break;
-    case 5: hipLaunchKernelGGL((msd_kernel<5>), grid, dim3(kBlock), 0, s, series, n_frames, n_lags, out); break;
-    default: hipLaunchKernelGGL((msd_kernel<6>), grid, dim3(kBlock), 0, s, series, n_frames, n_lags, out); break;
-    }
+    if (lag_blocks<WideMsd>(n_lags) * n_bodies * k >= kFillBlocks)
+        hipLaunchKernelGGL((msd_kernel<WideMsd>), dim3(lag_blocks<WideMsd>(n_lags), n_bodies, k),
+                           dim3(WideMsd::threads), 0, (hipStream_t)stream, series, n_frames, k,
+                           n_lags, out);
+    else
+        hipLaunchKernelGGL((msd_kernel<NarrowMsd>), dim3(lag_blocks<NarrowMsd>(n_lags), n_bodies, k),
+                           dim3(NarrowMsd::threads), 0, (hipStream_t)stream, series, n_frames, k,
+                           n_lags, out);
     return launched();
 }
 
@@ -474,9 +845,15 @@ int lb_traj_rotation_msd(const double* traj, int32_t n_frames, int32_t n_bodies,
     if (!frames_ok(traj, n_frames, n_bodies) || !ref_body || !out || n_lags < 1 ||
         n_lags >= n_frames || n_bodies > 65535)
         return LB_ERR_ARG;
-    hipLaunchKernelGGL(rotation_msd_kernel, dim3((n_lags + kLagBlock - 1) / kLagBlock, n_bodies),
-                       dim3(kBlock), 0,
-                       (hipStream_t)stream, traj, n_frames, n_bodies, ref_body, n_lags, out);
+    if (2 * lag_blocks<WideAngles>(n_lags) * n_bodies >= kFillBlocks)
+        hipLaunchKernelGGL((rotation_msd_kernel<WideAngles>),
+                           dim3(lag_blocks<WideAngles>(n_lags), n_bodies), dim3(WideAngles::threads),
+                           0, (hipStream_t)stream, traj, n_frames, n_bodies, ref_body, n_lags, out);
+    else
+        hipLaunchKernelGGL((rotation_msd_kernel<NarrowAngles>),
+                           dim3(lag_blocks<NarrowAngles>(n_lags), n_bodies),
+                           dim3(NarrowAngles::threads), 0, (hipStream_t)stream, traj, n_frames,
+                           n_bodies, ref_body, n_lags, out);
     return launched();
 }
 
@@ -489,14 +866,22 @@ int lb_traj_binned_msd(const double* series, const double* radial, int32_t n_fra
         return LB_ERR_ARG;
     hipStream_t s = (hipStream_t)stream;
     if (n_bins <= kTileBins && n_bodies <= 65535) {
-        if (hipMemsetAsync(sums, 0, sizeof(double) * k * n_bins * (size_t)n_lags, s) != hipSuccess ||
-            hipMemsetAsync(counts, 0, sizeof(double) * n_bins * (size_t)n_lags, s) != hipSuccess)
-            return LB_ERR_HIP;
-        const dim3 tiles((n_lags + kLagBlock - 1) / kLagBlock, n_bodies);
-        switch (k) {
-        case 1: hipLaunchKernelGGL((binned_msd_tiled_kernel<1>), tiles, dim3(kBlock), 0, s, series, radial, n_frames, edges, n_bins, n_lags, sums, counts); break;
-        case 2: hipLaunchKernelGGL((binned_msd_tiled_kernel<2>), tiles, dim3(kBlock), 0, s, series, radial, n_frames, edges, n_bins, n_lags, sums, counts); break;
-        default: hipLaunchKernelGGL((binned_msd_tiled_kernel<3>), tiles, dim3(kBlock), 0, s, series, radial, n_frames, edges, n_bins, n_lags, sums, counts); break;
+        const int64_t n_sums = (int64_t)k * n_bins * n_lags, n_counts = (int64_t)n_bins * n_lags;
+        hipLaunchKernelGGL(zero_sums_kernel, dim3((unsigned)((n_sums + n_counts + kBlock - 1) / kBlock)),
+                           dim3(kBlock), 0, s, sums, n_sums, counts, n_counts);
+        // 256 lags per workgroup, or 64 where most of 256 would be past the last lag
+        if (n_lags > 128) {
+            switch (k) {
+            case 1: launch_binned<1, 4>(series, radial, n_frames, n_bodies, edges, n_bins, n_lags, sums, counts, s); break;
+            case 2: launch_binned<2, 4>(series, radial, n_frames, n_bodies, edges, n_bins, n_lags, sums, counts, s); break;
+            default: launch_binned<3, 4>(series, radial, n_frames, n_bodies, edges, n_bins, n_lags, sums, counts, s); break;
+            }
+        } else {
+            switch (k) {
+            case 1: launch_binned<1, 1>(series, radial, n_frames, n_bodies, edges, n_bins, n_lags, sums, counts, s); break;
+            case 2: launch_binned<2, 1>(series, radial, n_frames, n_bodies, edges, n_bins, n_lags, sums, counts, s); break;
+            default: launch_binned<3, 1>(series, radial, n_frames, n_bodies, edges, n_bins, n_lags, sums, counts, s); break;
+            }
         }
         return launched();
     }

@@ -155,3 +155,40 @@ def test_recorded_simulation_trajectory():
     lab1 = _host(GA.msd(lab_g, 1))[:, 0, :].sum(axis=1)
     body1 = _host(GA.msd(body_g[:, :, :3].contiguous(), 1))[:, 0, :].sum(axis=1)
     assert np.abs(lab1 - body1).max() <= 1e-12 * lab1.max()
+
+
+@pytest.mark.parametrize("n_frames,n_bodies,n_lags",
+                         [(2, 3, 1), (512, 2, 130), (513, 1, 512), (514, 2, 17), (1026, 1, 1025),
+                          (300, 260, 20)])
+def test_tile_and_segment_edges(n_frames, n_bodies, n_lags):
+    """Frames around the 512 intervals of a segment of the series, lags around the 16 and 128 of
+    a workgroup, the last lag, and bodies enough for the wide lag blocks."""
+    centre = (32.0, 30.0)
+    traj = W.synthetic_trajectory(n_frames, n_bodies, seed=n_frames + n_lags, centre=centre,
+                                  rot_step=0.2)
+    ref = np.random.default_rng(9).normal(size=(n_bodies, 3))
+    _compare_all(traj, centre, n_lags, [0.0, 3.0, 5.0, 100.0], ref)
+
+
+@pytest.mark.parametrize("n_lags", [60, 300])     # one lag per lane, four
+def test_binned_msd_bin_of_every_frame_its_own(n_lags):
+    """Bins that change with every origin (and origins outside all of them)."""
+    rng = np.random.default_rng(12)
+    F, B = 1300, 2
+    series = np.cumsum(rng.normal(size=(F, B, 3)), axis=0)
+    radial = rng.uniform(0.0, 10.0, size=(F, B))
+    edges = [0.5, 2.0, 3.0, 5.0, 6.0, 8.0, 9.0]
+    sg, cg = GA.binned_msd(_dev(series.transpose(1, 0, 2)), _dev(radial.T), edges, n_lags)
+    so, co = OA.binned_msd(series, radial, edges, n_lags)
+    assert np.array_equal(_host(cg), co), "bin counts"
+    _close(_host(sg) / np.abs(so).max(), so / np.abs(so).max(), 1e-10, "binned msd")
+
+
+def test_non_finite_pose_reaches_the_lags_that_use_it():
+    traj = W.synthetic_trajectory(700, 2, seed=21)
+    traj[400, 1, 3:] = np.nan
+    ref = np.array([[1.0, 0.0, 0.0], [0.0, 1.0, 0.5]])
+    g = _host(GA.rotation_msd(_dev(traj), ref, 450))
+    o = OA.rotation_msd(traj, ref, 450)
+    assert np.array_equal(np.isnan(g), np.isnan(o))
+    assert np.abs(g - o)[~np.isnan(o)].max() <= 1e-8 * np.nanmax(o)
