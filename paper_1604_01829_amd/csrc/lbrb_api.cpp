@@ -146,6 +146,7 @@ bool make_plan(const lb_params* p, const lb_replica* reps, int32_t n, Plan& pl)
 struct ReplicaHost {
     int group = 0;            // 0 = dense tiles, 1 = masked tiles
     int64_t n_holes = 0;      // boundary nodes stored inside row spans (lbrb_walls.h)
+    std::vector<uint8_t> hole_tiles;   // per tile: 1 if it holds one (empty: no holes)
     int32_t tile0 = 0, n_tiles = 0;
     std::vector<int32_t> bodies;
     std::vector<uint8_t> mask;      // boundary mask as set (wall ids), empty = all fluid
@@ -191,7 +192,7 @@ struct lb_ctx {
     long long* gforce = nullptr;
     uint8_t* flags = nullptr;
     uint8_t* hole = nullptr;          // per node: wall id of a hole, else 0
-    NodeTile* d_hole_tiles = nullptr;  // the tiles of replicas with holes
+    NodeTile* d_hole_tiles = nullptr;  // the tiles that hold holes
     std::vector<NodeTile> hole_tiles;
     Body* d_bodies = nullptr;
     Bead* d_beads = nullptr;
@@ -529,12 +530,11 @@ void rebuild_tiles(lb_ctx* c)
 
 int upload_tables(lb_ctx* c)
 {
-    // the tiles of replicas with holes, for the mirror launch
+    // the tiles that hold holes, for the mirror launch
     c->hole_tiles.clear();
     for (int r = 0; r < c->n_rep; ++r)
-        if (c->reps[r].masked == 2)
-            c->hole_tiles.insert(c->hole_tiles.end(), c->tiles[1].begin() + c->rh[r].tile0,
-                                 c->tiles[1].begin() + c->rh[r].tile0 + c->rh[r].n_tiles);
+        for (int32_t k = 0; k < (int32_t)c->rh[r].hole_tiles.size(); ++k)
+            if (c->rh[r].hole_tiles[k]) c->hole_tiles.push_back(c->tiles[1][c->rh[r].tile0 + k]);
     if (!c->hole_tiles.empty())
         HIP_TRY(c, hipMemcpyAsync(c->d_hole_tiles, c->hole_tiles.data(),
                                   sizeof(NodeTile) * c->hole_tiles.size(), hipMemcpyHostToDevice,
@@ -1382,6 +1382,10 @@ int lb_set_boundary_mask(lb_ctx* c, int32_t replica, const uint8_t* mask)
     R.inv_nx = 1.0 / R.nx;
     R.inv_ny = 1.0 / R.ny;
     H.n_holes = n_holes;
+    H.hole_tiles.assign(n_holes > 0 ? (m.holes.size() + kNodeBlock - 1) / kNodeBlock : 0, 0);
+    if (n_holes > 0)
+        for (size_t k = 0; k < m.holes.size(); ++k)
+            if (m.holes[k]) H.hole_tiles[k / kNodeBlock] = 1;
     H.links.swap(links);
     destroy_graphs(c);
     rebuild_tiles(c);
