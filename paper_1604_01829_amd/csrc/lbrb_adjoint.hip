@@ -33,33 +33,39 @@
 
 namespace lbrb {
 
-template <typename Real, bool MASKED>
+// One thread per fluid node, one tile per workgroup, tiles dealt to XCDs in runs as in the node
+// update (whose loads and addressing it shares).  lamF is stored for the nodes whose spread
+// force is flagged only: those of the beads' stencils, the only ones the bead pass reads.
+// Bound by its loads and stores (228 B per node in FP32) and, on small boxes, by the launch: a
+// 64^3 box in FP32 takes 12.7 us (14.9 with dense transforms, the lamF of every node and
+// the tiles in launch order).
+template <typename Real, bool MASKED, bool NARROW>
 __global__ __launch_bounds__(kNodeBlock) void adj_node_kernel(const AdjArgs<Real> A)
 {
     const StepArgs<Real>& a = A.a;
-    const NodeTile t = a.tiles[blockIdx.x];
-    if ((int)threadIdx.x >= t.count) return;
+    __shared__ RowDesc tile_rows[MASKED ? kNodeBlock : 1];
+    const NodeTile t = a.tiles[xcd_tile(blockIdx.x, gridDim.x)];
     const ReplicaDesc R = a.reps[t.replica];
     const int64_t local = t.begin + threadIdx.x;
     int x, y, z;
     RowDesc self;
-    locate<MASKED>(R, a.rows, t.row_lo, t.row_hi, local, x, y, z, self);
-    if (MASKED && R.masked == 2 && a.hole[R.base + local] != 0) {
+    locate_tile<MASKED>(R, a.rows, t, local, tile_rows, x, y, z, self);
+    if ((int)threadIdx.x >= t.count) return;
+    const int64_t g = R.base + local;
+    if (MASKED && R.masked == 2 && a.hole[g] != 0) {
         // a hole is a boundary node: no adjoint of its own (the transposed mirror later fills
         // the slots its fluid neighbours read)
-        const int64_t g = R.base + local;
 #pragma unroll
         for (int i = 0; i < Q; ++i) A.lam_cur[pop_at(i, g)] = (Real)0;
-        for (int ax = 0; ax < 3; ++ax) A.lamF[(int64_t)ax * a.N + g] = (Real)0;
         if (a.flags[g]) a.flags[g] = 0;
         return;
     }
+    const uint8_t flag = a.flags[g];   // before the populations: its wait is covered by theirs
     Real d[Q], lam[Q];
-    pull<Real, MASKED, 1>(a.src, a.N, R, a.rowinfo, x, y, z, local, self, d);
-    pull<Real, MASKED, -1>(A.lam_next, a.N, R, a.rowinfo, x, y, z, local, self, lam);
-    const int64_t g = R.base + local;
+    pull<Real, MASKED, 1, NARROW>(a.src, a.N, R, a.rowinfo, x, y, z, local, self, d);
+    pull<Real, MASKED, -1, NARROW>(A.lam_next, a.N, R, a.rowinfo, x, y, z, local, self, lam);
     Real F[3] = {a.gext[0], a.gext[1], a.gext[2]};
-    if (a.flags[g]) {
+    if (flag) {
         take_spread_force<Real>(a.gforce, g, F);
         a.flags[g] = 0;
     }
@@ -67,8 +73,10 @@ __global__ __launch_bounds__(kNodeBlock) void adj_node_kernel(const AdjArgs<Real
     collide_vjp<Real>(a.cp, d, F, lam, lF);
 #pragma unroll
     for (int i = 0; i < Q; ++i) A.lam_cur[pop_at(i, g)] = lam[i];
+    if (flag) {
 #pragma unroll
-    for (int ax = 0; ax < 3; ++ax) A.lamF[(int64_t)ax * a.N + g] = lF[ax];
+        for (int ax = 0; ax < 3; ++ax) A.lamF[(int64_t)ax * a.N + g] = lF[ax];
+    }
 }
 
 template <typename Real, bool FREE>
@@ -77,14 +85,25 @@ __global__ __launch_bounds__(kAdjBeadBlock) void adj_bead_kernel(const AdjArgs<R
     adj_bead_lanes<Real, FREE>(A, blockIdx.x * kAdjBeadBlock + threadIdx.x);
 }
 
+template <typename Real, bool NARROW>
+void launch_adjoint_nodes(const AdjArgs<Real>& A, bool masked, hipStream_t s)
+{
+    const dim3 grid(A.a.n_tiles), block(kNodeBlock);
+    if (masked) hipLaunchKernelGGL((adj_node_kernel<Real, true, NARROW>), grid, block, 0, s, A);
+    else hipLaunchKernelGGL((adj_node_kernel<Real, false, NARROW>), grid, block, 0, s, A);
+}
+
 template <typename Real>
 void launch_adjoint_step(const AdjArgs<Real>& A, bool masked, hipStream_t s)
 {
-    const dim3 block(kNodeBlock);
-    if (A.a.n_tiles > 0) {
-        if (masked) hipLaunchKernelGGL((adj_node_kernel<Real, true>), dim3(A.a.n_tiles), block, 0, s, A);
-        else hipLaunchKernelGGL((adj_node_kernel<Real, false>), dim3(A.a.n_tiles), block, 0, s, A);
+    if (A.a.n_tiles <= 0) return;
+    if constexpr (sizeof(Real) == 4) {   // 32-bit offsets as in the node update
+        if (A.a.narrow) {
+            launch_adjoint_nodes<Real, true>(A, masked, s);
+            return;
+        }
     }
+    launch_adjoint_nodes<Real, false>(A, masked, s);
 }
 
 template <typename Real>

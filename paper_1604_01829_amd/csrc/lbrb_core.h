@@ -239,129 +239,8 @@ LBRB_HD void collide(const CollideParams<Real>& P, Real d[Q], const Real F[3], c
     }
 }
 
-// ------------------------------------------------------------------ collision adjoint
-// Orthogonal basis vector e_k at velocity c_i and its norm b_k = sum_i w_i e_k(c_i)^2.
-LBRB_HD double basis_e(int k, int i)
-{
-    const double cx = cx_of(i), cy = cy_of(i), cz = cz_of(i), c2 = cx * cx + cy * cy + cz * cz;
-    switch (k) {
-    case 0: return 1.0;
-    case 1: return cx;
-    case 2: return cy;
-    case 3: return cz;
-    case 4: return c2 - 1.0;
-    case 5: return 3.0 * cx * cx - c2;
-    case 6: return cy * cy - cz * cz;
-    case 7: return cx * cy;
-    case 8: return cy * cz;
-    case 9: return cz * cx;
-    case 10: return (3.0 * c2 - 5.0) * cx;
-    case 11: return (3.0 * c2 - 5.0) * cy;
-    case 12: return (3.0 * c2 - 5.0) * cz;
-    case 13: return (cy * cy - cz * cz) * cx;
-    case 14: return (cz * cz - cx * cx) * cy;
-    case 15: return (cx * cx - cy * cy) * cz;
-    case 16: return 3.0 * c2 * c2 - 6.0 * c2 + 1.0;
-    case 17: return (2.0 * c2 - 3.0) * (3.0 * cx * cx - c2);
-    default: return (2.0 * c2 - 3.0) * (cy * cy - cz * cz);
-    }
-}
-LBRB_HD double basis_b(int k)
-{
-    constexpr double b[Q] = {1.0, 1.0 / 3, 1.0 / 3, 1.0 / 3, 2.0 / 3, 4.0 / 3, 4.0 / 9, 1.0 / 9,
-                             1.0 / 9, 1.0 / 9, 2.0 / 3, 2.0 / 3, 2.0 / 3, 2.0 / 9, 2.0 / 9, 2.0 / 9,
-                             2.0, 4.0 / 3, 4.0 / 9};
-    return b[k];
-}
-
-// Vector-Jacobian product of the deterministic collision: given lam (adjoint of the
-// post-collision populations) return the adjoints of the pre-collision populations (in lam,
-// overwritten) and of the force density (lamF).  d: shifted pre-collision populations.
-// The derivative runs backwards through: back-transform, relaxation towards the equilibrium
-// of (rho, u) plus the force source, u = (j + F/2)/rho, and the forward transform.
-template <typename Real>
-LBRB_HD void collide_vjp(const CollideParams<Real>& P, const Real d[Q], const Real F[3], Real lam[Q],
-                         Real lamF[3])
-{
-    Real m[Q];
-#pragma unroll
-    for (int k = 0; k < Q; ++k) {
-        Real acc = 0;
-#pragma unroll
-        for (int i = 0; i < Q; ++i) acc += (Real)basis_e(k, i) * d[i];
-        m[k] = acc;
-    }
-    const Real rho = P.rho0 + m[0];
-    const Real u[3] = {(m[1] + (Real)0.5 * F[0]) / rho, (m[2] + (Real)0.5 * F[1]) / rho,
-                       (m[3] + (Real)0.5 * F[2]) / rho};
-    const Real ux = u[0], uy = u[1], uz = u[2];
-    Real ls[Q];
-#pragma unroll
-    for (int k = 0; k < Q; ++k) {
-        Real acc = 0;
-#pragma unroll
-        for (int i = 0; i < Q; ++i) acc += (Real)(basis_e(k, i) * weight_of(i)) * lam[i];
-        ls[k] = acc * (Real)(1.0 / basis_b(k));
-    }
-    Real lm[Q];
-    lm[0] = ls[0];
-    Real lrho = 0, lu[3] = {0, 0, 0};
-    for (int a = 0; a < 3; ++a) { lm[1 + a] = ls[1 + a]; lamF[a] = ls[1 + a]; }
-    // relaxation rates per mode
-#pragma unroll
-    for (int k = 4; k < Q; ++k) {
-        const Real g = k == 4 ? P.g_bulk : (k <= 9 ? P.g_shear : (k <= 15 ? P.g_odd : P.g_even));
-        lm[k] = g * ls[k];
-    }
-    // stress modes: equilibrium (via rho and u) and force source (via u and F)
-    const Real Ab = ((Real)1 - P.g_bulk) * ls[4], Bb = P.h_bulk * ls[4];
-    Real A[10], B[10];
-    for (int k = 5; k <= 9; ++k) { A[k] = ((Real)1 - P.g_shear) * ls[k]; B[k] = P.h_shear * ls[k]; }
-    // k = 4: e = rho u.u, S = 2 u.F
-    lrho += Ab * (ux * ux + uy * uy + uz * uz);
-    for (int a = 0; a < 3; ++a) { lu[a] += Ab * (Real)2 * rho * u[a] + Bb * (Real)2 * F[a]; lamF[a] += Bb * (Real)2 * u[a]; }
-    // k = 5: e = rho (2ux^2 - uy^2 - uz^2), S = 2 (2 ux Fx - uy Fy - uz Fz)
-    lrho += A[5] * ((Real)2 * ux * ux - uy * uy - uz * uz);
-    lu[0] += A[5] * (Real)4 * rho * ux + B[5] * (Real)4 * F[0];
-    lu[1] -= A[5] * (Real)2 * rho * uy + B[5] * (Real)2 * F[1];
-    lu[2] -= A[5] * (Real)2 * rho * uz + B[5] * (Real)2 * F[2];
-    lamF[0] += B[5] * (Real)4 * ux; lamF[1] -= B[5] * (Real)2 * uy; lamF[2] -= B[5] * (Real)2 * uz;
-    // k = 6: e = rho (uy^2 - uz^2), S = 2 (uy Fy - uz Fz)
-    lrho += A[6] * (uy * uy - uz * uz);
-    lu[1] += A[6] * (Real)2 * rho * uy + B[6] * (Real)2 * F[1];
-    lu[2] -= A[6] * (Real)2 * rho * uz + B[6] * (Real)2 * F[2];
-    lamF[1] += B[6] * (Real)2 * uy; lamF[2] -= B[6] * (Real)2 * uz;
-    // k = 7: e = rho ux uy, S = ux Fy + uy Fx
-    lrho += A[7] * ux * uy;
-    lu[0] += A[7] * rho * uy + B[7] * F[1]; lu[1] += A[7] * rho * ux + B[7] * F[0];
-    lamF[0] += B[7] * uy; lamF[1] += B[7] * ux;
-    // k = 8: e = rho uy uz, S = uy Fz + uz Fy
-    lrho += A[8] * uy * uz;
-    lu[1] += A[8] * rho * uz + B[8] * F[2]; lu[2] += A[8] * rho * uy + B[8] * F[1];
-    lamF[1] += B[8] * uz; lamF[2] += B[8] * uy;
-    // k = 9: e = rho uz ux, S = uz Fx + ux Fz
-    lrho += A[9] * uz * ux;
-    lu[0] += A[9] * rho * uz + B[9] * F[2]; lu[2] += A[9] * rho * ux + B[9] * F[0];
-    lamF[0] += B[9] * uz; lamF[2] += B[9] * ux;
-    // u = (j + F/2) / rho
-    const Real irho = (Real)1 / rho;
-    for (int a = 0; a < 3; ++a) {
-        lm[1 + a] += lu[a] * irho;
-        lamF[a] += (Real)0.5 * lu[a] * irho;
-        lrho -= lu[a] * u[a] * irho;
-    }
-    lm[0] += lrho;
-    // m = E f
-#pragma unroll
-    for (int i = 0; i < Q; ++i) {
-        Real acc = 0;
-#pragma unroll
-        for (int k = 0; k < Q; ++k) acc += (Real)basis_e(k, i) * lm[k];
-        lam[i] = acc;
-    }
-}
-
-// density and momentum of shifted populations
+// density and momentum of shifted populations (the zero velocity components left out: a
+// product with zero is not the compiler's to drop)
 template <typename Real>
 LBRB_HD void density_momentum(const Real d[Q], Real& drho, Real j[3])
 {
@@ -369,11 +248,146 @@ LBRB_HD void density_momentum(const Real d[Q], Real& drho, Real j[3])
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
         r += d[i];
-        x += (Real)cx_of(i) * d[i];
-        y += (Real)cy_of(i) * d[i];
-        z += (Real)cz_of(i) * d[i];
+        if (cx_of(i) != 0) x += (Real)cx_of(i) * d[i];
+        if (cy_of(i) != 0) y += (Real)cy_of(i) * d[i];
+        if (cz_of(i) != 0) z += (Real)cz_of(i) * d[i];
     }
     drho = r; j[0] = x; j[1] = y; j[2] = z;
+}
+
+// ------------------------------------------------------------------ collision adjoint
+// The basis of collide: t[k] = sum_i e_k(c_i) p_i over sums and differences of opposite pairs
+// (p: the rest value, then each pair's sum and difference).
+template <typename Real>
+struct Pairs {
+    Real rest, s[9], d[9];   // pairs x, y, z, (7,8), (9,10), (11,12), (13,14), (15,16), (17,18)
+};
+
+template <typename Real>
+LBRB_HD void mode_sums(const Pairs<Real>& p, Real t[Q])
+{
+    const Real *s = p.s, *d = p.d;
+    const Real sax = s[0] + s[1] + s[2];
+    const Real sxy = s[3] + s[4], sxz = s[5] + s[6], syz = s[7] + s[8];
+    const Real sdg = sxy + sxz + syz;
+    const Real two = 2;
+    t[0] = p.rest + sax + sdg;
+    t[1] = d[0] + d[3] + d[4] + d[5] + d[6];
+    t[2] = d[1] + d[3] - d[4] + d[7] + d[8];
+    t[3] = d[2] + d[5] - d[6] + d[7] - d[8];
+    t[4] = sdg - p.rest;
+    t[5] = two * s[0] - s[1] - s[2] + sxy + sxz - two * syz;
+    t[6] = s[1] - s[2] + sxy - sxz;
+    t[7] = s[3] - s[4];
+    t[8] = s[7] - s[8];
+    t[9] = s[5] - s[6];
+    t[10] = d[3] + d[4] + d[5] + d[6] - two * d[0];
+    t[11] = d[3] - d[4] + d[7] + d[8] - two * d[1];
+    t[12] = d[5] - d[6] + d[7] - d[8] - two * d[2];
+    t[13] = d[3] + d[4] - d[5] - d[6];
+    t[14] = d[4] - d[3] + d[7] + d[8];
+    t[15] = d[5] - d[6] - d[7] + d[8];
+    t[16] = p.rest - two * sax + sdg;
+    t[17] = s[1] + s[2] - two * s[0] + sxy + sxz - two * syz;
+    t[18] = s[2] - s[1] + sxy - sxz;
+}
+
+// its transpose: out[i] = sum_k e_k(c_i) a_k
+template <typename Real>
+LBRB_HD void mode_spread(const Real a[Q], Real out[Q])
+{
+    const Real two = 2;
+    auto pair = [&](int i, Real e, Real o) { out[i] = e + o; out[i + 1] = e - o; };
+    const Real ax = a[0] - two * a[16];                      // common to the axis pairs
+    out[0] = a[0] - a[4] + a[16];
+    pair(1, ax + two * (a[5] - a[17]), a[1] - two * a[10]);
+    pair(3, ax - a[5] + a[6] + a[17] - a[18], a[2] - two * a[11]);
+    pair(5, ax - a[5] - a[6] + a[17] + a[18], a[3] - two * a[12]);
+    const Real dg = a[0] + a[4] + a[16];                     // common to the diagonal pairs
+    const Real e57 = dg + a[5] + a[17], e68 = a[6] + a[18];
+    const Real exy = e57 + e68, exz = e57 - e68, eyz = dg - two * (a[5] + a[17]);
+    const Real px = a[1] + a[10], py = a[2] + a[11], pz = a[3] + a[12];
+    pair(7, exy + a[7], px + py + a[13] - a[14]);
+    pair(9, exy - a[7], px - py + a[13] + a[14]);
+    pair(11, exz + a[9], px + pz - a[13] + a[15]);
+    pair(13, exz - a[9], px - pz - a[13] - a[15]);
+    pair(15, eyz + a[8], py + pz + a[14] - a[15]);
+    pair(17, eyz - a[8], py - pz + a[14] + a[15]);
+}
+
+// Vector-Jacobian product of the deterministic collision: given lam (adjoint of the
+// post-collision populations) return the adjoints of the pre-collision populations (in lam,
+// overwritten) and of the force density (lamF).  d: shifted pre-collision populations.
+// The derivative runs backwards through: back-transform, relaxation towards the equilibrium
+// of (rho, u) plus the force source, u = (j + F/2)/rho, and the forward transform.  Both
+// transforms run on sums and differences of opposite populations (as dense 19 x 19 products,
+// whose zero entries the compiler must keep, they were 1083 of the node pass's multiply-adds).
+template <typename Real>
+LBRB_HD void collide_vjp(const CollideParams<Real>& P, const Real d[Q], const Real F[3], Real lam[Q],
+                         Real lamF[3])
+{
+    Real drho, j[3];
+    density_momentum<Real>(d, drho, j);
+    const Real rho = P.rho0 + drho, irho = (Real)1 / rho;
+    const Real u[3] = {(j[0] + (Real)0.5 * F[0]) * irho, (j[1] + (Real)0.5 * F[1]) * irho,
+                       (j[2] + (Real)0.5 * F[2]) * irho};
+    const Real ux = u[0], uy = u[1], uz = u[2];
+    // adjoint of the post-collision modes: ls_k = sum_i w_i e_k(c_i) lam_i / b_k
+    Pairs<Real> p;
+    p.rest = (Real)(1.0 / 3.0) * lam[0];
+#pragma unroll
+    for (int q = 0; q < 9; ++q) {
+        const Real w = q < 3 ? (Real)(1.0 / 18.0) : (Real)(1.0 / 36.0);
+        p.s[q] = w * (lam[2 * q + 1] + lam[2 * q + 2]);
+        p.d[q] = w * (lam[2 * q + 1] - lam[2 * q + 2]);
+    }
+    Real ls[Q];
+    mode_sums<Real>(p, ls);
+    // 1 / b_k of the orthogonal basis
+    constexpr double ib[Q] = {1.0, 3.0, 3.0, 3.0, 1.5, 0.75, 2.25, 9.0, 9.0, 9.0,
+                              1.5, 1.5, 1.5, 4.5, 4.5, 4.5, 0.5, 0.75, 2.25};
+#pragma unroll
+    for (int k = 1; k < Q; ++k) ls[k] *= (Real)ib[k];
+    Real lm[Q];
+    lm[0] = ls[0];
+    for (int a = 0; a < 3; ++a) { lm[1 + a] = ls[1 + a]; lamF[a] = ls[1 + a]; }
+    // relaxation rates per mode
+#pragma unroll
+    for (int k = 4; k < Q; ++k) {
+        const Real g = k == 4 ? P.g_bulk : (k <= 9 ? P.g_shear : (k <= 15 ? P.g_odd : P.g_even));
+        lm[k] = g * ls[k];
+    }
+    // Stress modes: equilibrium e_k = rho u.M_k u and force source S_k = 2 u.M_k F with the
+    // symmetric matrices M_k of the modes' second moments; A = sum_k (1 - g_k) ls_k M_k and
+    // B = sum_k h_k ls_k M_k, so that the adjoints are 2 rho A u + 2 B F to u, u.A u to rho and
+    // 2 B u to F.
+    const Real ab = ((Real)1 - P.g_bulk) * ls[4], bb = P.h_bulk * ls[4];
+    const Real as = (Real)1 - P.g_shear, bs = P.h_shear;
+    // diagonal entries of the traceless part (modes 5 and 6) and the off-diagonal halves
+    const Real dxx = (Real)2 * ls[5], dyy = ls[6] - ls[5], dzz = -(ls[6] + ls[5]);
+    const Real oxy = (Real)0.5 * ls[7], oyz = (Real)0.5 * ls[8], ozx = (Real)0.5 * ls[9];
+    const Real Tu[3] = {dxx * ux + oxy * uy + ozx * uz, oxy * ux + dyy * uy + oyz * uz,
+                        ozx * ux + oyz * uy + dzz * uz};
+    const Real TF[3] = {dxx * F[0] + oxy * F[1] + ozx * F[2], oxy * F[0] + dyy * F[1] + oyz * F[2],
+                        ozx * F[0] + oyz * F[1] + dzz * F[2]};
+    Real lrho = 0, lu[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const Real Au = ab * u[a] + as * Tu[a];
+        lrho += u[a] * Au;
+        lu[a] = (Real)2 * (rho * Au + (bb * F[a] + bs * TF[a]));
+        lamF[a] += (Real)2 * (bb * u[a] + bs * Tu[a]);
+    }
+    // u = (j + F/2) / rho
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const Real v = lu[a] * irho;
+        lm[1 + a] += v;
+        lamF[a] += (Real)0.5 * v;
+        lrho -= v * u[a];
+    }
+    lm[0] += lrho;
+    mode_spread<Real>(lm, lam);   // m = E f
 }
 
 // ------------------------------------------------------------------ rigid bodies (FP64)
