@@ -229,6 +229,8 @@ struct lb_ctx {
     int32_t graph_steps = 100;
     hipGraphExec_t gexec[2] = {nullptr, nullptr};
     hipStream_t cap_stream = nullptr;
+    double* host_out = nullptr;       // pinned: the answer of lb_observables
+    size_t host_words = 0;
     // timing
     bool timing = false;
     int32_t store_policy = LB_STORES_AUTO;
@@ -1613,56 +1615,61 @@ int lb_observables(lb_ctx* c, int32_t replica, lb_totals* out, rb_state* bodies,
     if (!check_replica(c, replica)) return LB_ERR_ARG;
     const ReplicaDesc& R = c->reps[replica];
     const ReplicaHost& H = c->rh[replica];
-    const size_t real = is_f32(c) ? sizeof(float) : sizeof(double);
-    if (dev_rho_u)
-        HIP_TRY(c, hipMemsetAsync(dev_rho_u, 0, real * 4 * R.n_nodes, c->stream));
+    // pinned host memory for the answer, grown with the bodies (a device-to-host copy of pageable
+    // memory per array took 20-35 us each, three of them per call)
+    const size_t need = 8 + (size_t)kObserveBodyWords * (size_t)c->n_bodies;
+    if (c->host_words < need) {
+        if (c->host_out) {
+            HIP_TRY(c, hipStreamSynchronize(c->stream));
+            HIP_TRY(c, hipHostFree(c->host_out));
+            c->host_out = nullptr;
+            c->host_words = 0;
+        }
+        const size_t words = std::max(need, 8 + (size_t)kObserveBodyWords * 64);
+        HIP_TRY(c, hipHostMalloc((void**)&c->host_out, sizeof(double) * words, hipHostMallocDefault));
+        c->host_words = words;
+    }
+    const ObserveOut host{c->host_out, c->host_out + 8};
     if (is_f32(c)) {
         StepArgs<float> a = step_args<float>(c, H.group, c->cur);
-        launch_observe<float>(a, H.group == 1, H.tile0, H.n_tiles, (float*)dev_rho_u,
-                              c->d_partials, nullptr, c->stream);
+        launch_observe<float>(a, H.group == 1, H.tile0, H.n_tiles, replica, R.n_nodes,
+                              (float*)dev_rho_u, c->d_partials, nullptr, c->stream);
     } else {
         StepArgs<double> a = step_args<double>(c, H.group, c->cur);
-        launch_observe<double>(a, H.group == 1, H.tile0, H.n_tiles, (double*)dev_rho_u,
-                               c->d_partials, nullptr, c->stream);
+        launch_observe<double>(a, H.group == 1, H.tile0, H.n_tiles, replica, R.n_nodes,
+                               (double*)dev_rho_u, c->d_partials, nullptr, c->stream);
     }
     HIP_TRY(c, hipGetLastError());
-    std::vector<double> part(5 * (size_t)H.n_tiles);
-    if (H.n_tiles > 0)
-        HIP_TRY(c, hipMemcpyAsync(part.data(), c->d_partials, sizeof(double) * part.size(),
-                                  hipMemcpyDeviceToHost, c->stream));
-    std::vector<Body> bs(c->n_bodies);
-    if (c->n_bodies > 0)
-        HIP_TRY(c, hipMemcpyAsync(bs.data(), c->d_bodies, sizeof(Body) * c->n_bodies,
-                                  hipMemcpyDeviceToHost, c->stream));
-    DeviceHeader hdr{};
-    HIP_TRY(c, hipMemcpyAsync(&hdr, c->hdr, sizeof(DeviceHeader), hipMemcpyDeviceToHost, c->stream));
+    launch_observe_out(c->d_partials, H.n_tiles, c->hdr, c->d_bodies, c->n_bodies, replica, host,
+                       c->stream);
+    HIP_TRY(c, hipGetLastError());
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    double s[5] = {0, 0, 0, 0, 0};
-    for (int32_t t = 0; t < H.n_tiles; ++t)
-        for (int k = 0; k < 5; ++k) s[k] += part[5 * (size_t)t + k];
+    const double* s = host.totals;
+    const uint32_t err_flags = (uint32_t)s[5];
     lb_totals T{};
     T.mass = (double)(R.n_fluid - H.n_holes) * c->p.rho0 + s[0];
     for (int a = 0; a < 3; ++a) T.momentum[a] = s[1 + a];
     for (int32_t b : H.bodies) {
-        if (bs[b].fixed) continue;
-        for (int a = 0; a < 3; ++a) T.body_momentum[a] += bs[b].mass * bs[b].vel[a];
+        const double* w = host.bodies + (size_t)kObserveBodyWords * b;
+        if (w[kObserveBodyWords - 1] < 0.0) continue;   // fixed
+        for (int a = 0; a < 3; ++a) T.body_momentum[a] += w[kObserveBodyWords - 1] * w[7 + a];
     }
     T.step = c->step;
     T.finite = (s[4] == 0.0 && std::isfinite(T.mass)) ? 1 : 0;
     if (out) *out = T;
     if (bodies) {
         for (size_t k = 0; k < H.bodies.size(); ++k) {
-            const Body& B = bs[H.bodies[k]];
+            const double* w = host.bodies + (size_t)kObserveBodyWords * H.bodies[k];
             rb_state& o = bodies[k];
             for (int a = 0; a < 3; ++a) {
-                o.pos[a] = B.pos[a]; o.vel[a] = B.vel[a]; o.omega_body[a] = B.omega[a];
-                o.force[a] = B.force[a]; o.torque[a] = B.torque[a];
+                o.pos[a] = w[a]; o.vel[a] = w[7 + a]; o.omega_body[a] = w[10 + a];
+                o.force[a] = w[13 + a]; o.torque[a] = w[16 + a];
             }
-            for (int a = 0; a < 4; ++a) o.quat[a] = B.quat[a];
+            for (int a = 0; a < 4; ++a) o.quat[a] = w[3 + a];
         }
     }
     if (!T.finite) return fail(c, LB_ERR_UNSTABLE, "non-finite populations");
-    if (hdr.err_flags & 1u) return fail(c, LB_ERR_UNSTABLE, "spread force out of range");
+    if (err_flags & 1u) return fail(c, LB_ERR_UNSTABLE, "spread force out of range");
     return LB_OK;
 }
 
@@ -1710,12 +1717,12 @@ int lb_export_populations(lb_ctx* c, int32_t replica, double* dev_out)
     HIP_TRY(c, hipMemsetAsync(dev_out, 0, sizeof(double) * Q * R.n_nodes, c->stream));
     if (is_f32(c)) {
         StepArgs<float> a = step_args<float>(c, H.group, c->cur);
-        launch_observe<float>(a, H.group == 1, H.tile0, H.n_tiles, nullptr, nullptr, dev_out,
-                              c->stream);
+        launch_observe<float>(a, H.group == 1, H.tile0, H.n_tiles, replica, R.n_nodes, nullptr,
+                              nullptr, dev_out, c->stream);
     } else {
         StepArgs<double> a = step_args<double>(c, H.group, c->cur);
-        launch_observe<double>(a, H.group == 1, H.tile0, H.n_tiles, nullptr, nullptr, dev_out,
-                               c->stream);
+        launch_observe<double>(a, H.group == 1, H.tile0, H.n_tiles, replica, R.n_nodes, nullptr,
+                               nullptr, dev_out, c->stream);
     }
     HIP_TRY(c, hipGetLastError());
     HIP_TRY(c, hipStreamSynchronize(c->stream));
@@ -1941,6 +1948,7 @@ void lb_destroy(lb_ctx* c)
         if (e.b) (void)hipEventDestroy(e.b);
     }
     if (c->cap_stream) (void)hipStreamDestroy(c->cap_stream);
+    if (c->host_out) (void)hipHostFree(c->host_out);
     delete c;
 }
 

@@ -1038,11 +1038,37 @@ void launch_init_equilibrium(Real* f, int64_t N, const ReplicaDesc* reps, const 
 
 // ------------------------------------------------------------------ observables
 
+// fields of one node of the box, written whole: (rho, ux, uy, uz)
+template <typename Real>
+__device__ __forceinline__ void store_fields(Real* o, Real rho, Real ux, Real uy, Real uz)
+{
+    o[0] = rho; o[1] = ux; o[2] = uy; o[3] = uz;
+}
+
+// One workgroup per node tile; for a masked replica with fields, further workgroups write the
+// zeros of its boundary nodes, 256 nodes of the box each (so the array needs no clearing first).
 template <typename Real, bool MASKED>
 __global__ __launch_bounds__(kNodeBlock) void observe_kernel(const StepArgs<Real> a,
-                                                             const NodeTile* tiles, Real* fields,
+                                                             const NodeTile* tiles, int n_tiles,
+                                                             int replica, Real* fields,
                                                              double* partials, double* pops)
 {
+    if (MASKED && (int)blockIdx.x >= n_tiles) {
+        const ReplicaDesc R = a.reps[replica];
+        const int64_t dense = (int64_t)(blockIdx.x - n_tiles) * kNodeBlock + threadIdx.x;
+        if (dense >= R.n_nodes) return;
+        // box coordinates, then the storage's
+        const int bx = R.swap ? R.nz : R.nx;
+        const int64_t row = dense / bx;
+        const int x = (int)(dense - row * bx), z = (int)(row / R.ny), y = (int)(row - (int64_t)z * R.ny);
+        const int sx = R.swap ? z : x, sz = R.swap ? x : z;
+        const RowDesc rd = a.rowinfo[R.row_base + y + R.ny * sz];
+        const int off = sx - rd.xlo;
+        const bool stored = (unsigned)off < (unsigned)rd.len;
+        if (!stored || (R.masked == 2 && a.hole[R.base + rd.start + off] != 0))
+            store_fields<Real>(fields + 4 * dense, 0, 0, 0, 0);
+        return;
+    }
     __shared__ double part[kNodeBlock / 64][5];
     const NodeTile t = tiles[blockIdx.x];
     const ReplicaDesc R = a.reps[t.replica];
@@ -1062,9 +1088,9 @@ __global__ __launch_bounds__(kNodeBlock) void observe_kernel(const StepArgs<Real
         const int64_t dense = box_index(R, x, y, z);   // outputs in the box's own order
         if (fields) {
             const Real rho = a.cp.rho0 + drho;
-            Real* o = fields + 4 * dense;
-            o[0] = rho;
-            for (int ax = 0; ax < 3; ++ax) o[1 + ax] = (j[ax] + (Real)0.5 * a.gext[ax]) / rho;
+            store_fields<Real>(fields + 4 * dense, rho, (j[0] + (Real)0.5 * a.gext[0]) / rho,
+                               (j[1] + (Real)0.5 * a.gext[1]) / rho,
+                               (j[2] + (Real)0.5 * a.gext[2]) / rho);
         }
         if (pops) {
             for (int i = 0; i < Q; ++i)
@@ -1091,16 +1117,64 @@ __global__ __launch_bounds__(kNodeBlock) void observe_kernel(const StepArgs<Real
 
 template <typename Real>
 void launch_observe(const StepArgs<Real>& a, bool masked, int32_t tile0, int32_t n_tiles,
-                    Real* fields, double* partials, double* pops_out, hipStream_t s)
+                    int32_t replica, int64_t n_nodes, Real* fields, double* partials,
+                    double* pops_out, hipStream_t s)
 {
-    if (n_tiles <= 0) return;
     const NodeTile* tiles = a.tiles + tile0;
+    const int64_t zeros = masked && fields ? (n_nodes + kNodeBlock - 1) / kNodeBlock : 0;
+    const dim3 grid((unsigned)(n_tiles + zeros));
+    if (grid.x == 0) return;
     if (masked)
-        hipLaunchKernelGGL((observe_kernel<Real, true>), dim3(n_tiles), dim3(kNodeBlock), 0, s, a,
-                           tiles, fields, partials, pops_out);
+        hipLaunchKernelGGL((observe_kernel<Real, true>), grid, dim3(kNodeBlock), 0, s, a, tiles,
+                           n_tiles, replica, fields, partials, pops_out);
     else
-        hipLaunchKernelGGL((observe_kernel<Real, false>), dim3(n_tiles), dim3(kNodeBlock), 0, s, a,
-                           tiles, fields, partials, pops_out);
+        hipLaunchKernelGGL((observe_kernel<Real, false>), grid, dim3(kNodeBlock), 0, s, a, tiles,
+                           n_tiles, replica, fields, partials, pops_out);
+}
+
+// The answer of lb_observables in host memory: workgroup 0 adds the tiles' partial sums (each
+// thread every 256th tile, then shuffles and LDS: a fixed order) and copies the error flags, the
+// others copy the state of the replica's bodies, a thread per word, each to its global index.
+__global__ __launch_bounds__(256) void observe_out_kernel(const double* partials, int n_tiles,
+                                                          const DeviceHeader* hdr, const Body* bodies,
+                                                          int n_bodies, int replica, ObserveOut out)
+{
+    if (blockIdx.x > 0) {
+        const int e = (int)(blockIdx.x - 1) * 256 + threadIdx.x;
+        const int b = e / kObserveBodyWords, k = e % kObserveBodyWords;
+        if (b >= n_bodies || bodies[b].replica != replica) return;
+        // pos, quat, vel, omega, force, torque lead the record; then the mass, -1 for a fixed body
+        out.bodies[e] = k == kObserveBodyWords - 1 && bodies[b].fixed
+                            ? -1.0
+                            : reinterpret_cast<const double*>(bodies + b)[k];
+        return;
+    }
+    __shared__ double part[4][5];
+    double acc[5] = {0, 0, 0, 0, 0};
+    for (int t = threadIdx.x; t < n_tiles; t += 256)
+        for (int k = 0; k < 5; ++k) acc[k] += partials[5 * (int64_t)t + k];
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1)
+        for (int k = 0; k < 5; ++k) acc[k] += __shfl_down(acc[k], m, 64);
+    if ((threadIdx.x & 63) == 0)
+        for (int k = 0; k < 5; ++k) part[threadIdx.x >> 6][k] = acc[k];
+    __syncthreads();
+    if (threadIdx.x < 5) {
+        const int k = threadIdx.x;
+        out.totals[k] = (part[0][k] + part[1][k]) + (part[2][k] + part[3][k]);
+    }
+    if (threadIdx.x == 5) out.totals[5] = (double)hdr->err_flags;
+}
+
+void launch_observe_out(const double* partials, int n_tiles, const DeviceHeader* hdr,
+                        const Body* bodies, int n_bodies, int replica, const ObserveOut& out,
+                        hipStream_t s)
+{
+    static_assert(offsetof(Body, mass) == (kObserveBodyWords - 1) * sizeof(double),
+                  "the body's state leads its record, then its mass");
+    const int blocks = 1 + (n_bodies * kObserveBodyWords + 255) / 256;
+    hipLaunchKernelGGL(observe_out_kernel, dim3(blocks), dim3(256), 0, s, partials, n_tiles, hdr,
+                       bodies, n_bodies, replica, out);
 }
 
 // explicit instantiations
@@ -1121,9 +1195,9 @@ template void launch_init_equilibrium<float>(float*, int64_t, const ReplicaDesc*
 template void launch_init_equilibrium<double>(double*, int64_t, const ReplicaDesc*,
                                               const NodeTile*, int32_t, double, const double*,
                                               hipStream_t);
-template void launch_observe<float>(const StepArgs<float>&, bool, int32_t, int32_t, float*,
-                                    double*, double*, hipStream_t);
-template void launch_observe<double>(const StepArgs<double>&, bool, int32_t, int32_t, double*,
-                                     double*, double*, hipStream_t);
+template void launch_observe<float>(const StepArgs<float>&, bool, int32_t, int32_t, int32_t, int64_t,
+                                    float*, double*, double*, hipStream_t);
+template void launch_observe<double>(const StepArgs<double>&, bool, int32_t, int32_t, int32_t,
+                                     int64_t, double*, double*, double*, hipStream_t);
 
 }  // namespace lbrb

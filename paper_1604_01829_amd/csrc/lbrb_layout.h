@@ -226,11 +226,23 @@ void launch_set_step(int64_t* step_ptr, int64_t value, hipStream_t s);
 template <typename Real>
 void launch_init_equilibrium(Real* f, int64_t N, const ReplicaDesc* reps, const NodeTile* tiles,
                              int32_t n_tiles, Real rho0, const double u0[3], hipStream_t s);
-// per-replica observables over a tile range: fields (may be null), partial sums (5 doubles per
-// tile: drho, jx, jy, jz, nonfinite count), exported FP64 populations (may be null)
+// per-replica observables over a tile range: fields (may be null; zeros on the boundary nodes of
+// the replica's n_nodes included), partial sums (5 doubles per tile: drho, jx, jy, jz, nonfinite
+// count), exported FP64 populations (may be null)
 template <typename Real>
 void launch_observe(const StepArgs<Real>& a, bool masked, int32_t tile0, int32_t n_tiles,
-                    Real* fields, double* partials, double* pops_out, hipStream_t s);
+                    int32_t replica, int64_t n_nodes, Real* fields, double* partials,
+                    double* pops_out, hipStream_t s);
+// and what lb_observables hands out, written to host memory that the device can reach
+constexpr int kObserveBodyWords = 20;   // position, quaternion, velocity, omega, force, torque,
+                                        // mass (-1: fixed)
+struct ObserveOut {
+    double* totals;         // the 5 sums over the tiles, then the error flags
+    double* bodies;         // kObserveBodyWords per body of the context; the replica's are set
+};
+void launch_observe_out(const double* partials, int n_tiles, const DeviceHeader* hdr,
+                        const Body* bodies, int n_bodies, int replica, const ObserveOut& out,
+                        hipStream_t s);
 
 // ------------------------------------------------------------------ reverse pass
 // Arguments of one reverse step (deterministic fluid).  The forward state of the step is

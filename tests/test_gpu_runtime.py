@@ -287,3 +287,48 @@ def test_injected_nan_is_reported_and_a_checkpoint_restores_the_run_bitwise(case
             sim.inject_nan(0, *args)
         assert e.value.code == lbrb.LB_ERR_ARG
     sim.close()
+
+
+@pytest.mark.parametrize("precision", ["f32", "f64"])
+def test_observables_write_every_node_and_only_their_replica(precision):
+    """A field buffer holding other values: boundary nodes of a pore stored along z, of an obstacle
+    between fluid runs and of a box without fluid come back as zeros, and the bodies are the
+    replica's, whatever order they were added in."""
+    import torch
+    block = np.zeros((20, 13, 17), dtype=np.uint8)
+    block[5:9, 3:8, 4:9] = 1
+    masks = [W.pore_mask(21, 21, 40, 8.0), block, np.ones((6, 5, 7), dtype=np.uint8), None]
+    shapes = [m.shape[::-1] if m is not None else (9, 10, 11) for m in masks]
+    offs = W.sphere_beads(1.5, 30)
+    mass, inertia = W.solid_body_mass_inertia(1.0, 1.5, 1.5, 1.5)
+    params = lbrb.make_params(precision=precision, max_bodies=5, max_beads=5 * len(offs), kT=4e-5)
+    sim = lbrb.Simulation(params, lbrb.make_replicas([(s, 7 + k) for k, s in enumerate(shapes)]))
+    for r, m in enumerate(masks):
+        if m is not None:
+            sim.set_mask(r, m)
+    order = [(1, 0.3), (0, 0.1), (1, 0.2), (3, 0.4), (0, 0.5)]
+    for r, v in order:
+        sim.add_body(r, offs, mass, inertia, np.array(shapes[r]) / 2.0, vel=(0.001 * v, 0, 0),
+                     gamma=W.GAMMA_FREE, fixed=v == 0.4)
+    assert sim.row_axis(0) == 2
+    sim.step(3)
+    for r, m in enumerate(masks):
+        n = 4 * int(np.prod(shapes[r]))
+        buf = torch.full((n + 8,), 77.0, dtype=sim.dtype, device="cuda:0")
+        rc, tot, bodies = lbrb.lb_observables(sim.ctx, r, sim.n_bodies[r], buf.data_ptr(), check=False)
+        assert rc == 0
+        f = buf.cpu().numpy()
+        assert np.all(f[n:] == 77.0)
+        f = f[:n].reshape(*shapes[r][::-1], 4)
+        solid = np.zeros(f.shape[:3], bool) if m is None else m != 0
+        assert np.all(f[solid] == 0.0) and np.all(np.abs(f[~solid][:, 0] - 1.0) < 0.1)
+        # the sum over the fluid nodes, to the rounding of the fields
+        assert abs(tot.mass - float(f[..., 0].astype(np.float64).sum())) <= 1e-6 * max(1.0, tot.mass)
+        mine = [v for q, v in order if q == r]
+        assert len(bodies) == len(mine)
+        for b, v in zip(bodies, mine):
+            assert np.allclose(b.pos[:], np.array(shapes[r]) / 2.0, atol=0.1)
+        free = [b for b, v in zip(bodies, mine) if v != 0.4]
+        p = mass * np.sum([b.vel[:] for b in free], axis=0) if free else np.zeros(3)
+        assert np.allclose(tot.body_momentum[:], p, rtol=1e-12, atol=1e-18)
+    sim.close()
