@@ -322,6 +322,7 @@ StepArgs<Real> step_args_on(const lb_ctx* c, int group, const void* src, void* d
     a.gforce = c->gforce;
     a.flags = c->flags;
     a.hole = c->hole;
+    a.links = c->d_links;
     a.cp = collide_params<Real>(c->p);
     for (int ax = 0; ax < 3; ++ax) a.gext[ax] = (Real)c->p.g_ext[ax];
     a.step_ptr = nullptr;
@@ -448,9 +449,18 @@ hipError_t enqueue_node(lb_ctx* c, hipStream_t s, int src_buf, const int64_t* st
     return err;
 }
 
+// the moving-wall links of a node update that left them out (workgroups of several tiles)
+template <typename Real>
+hipError_t enqueue_links(lb_ctx* c, hipStream_t s, void* f)
+{
+    if (c->n_links == 0 || c->tune.tiles_per_wg != kWideTiles) return hipSuccess;
+    launch_wall_links<Real>((Real*)f, c->d_links, c->n_links, s);
+    return hipGetLastError();
+}
+
 // One serial fluid step on stream s: the couplings, then the node update of each tile group
-// (the first node launch also finishes the bodies), then the moving-wall links.  Returns the
-// first HIP error of the enqueued calls.
+// (the first node launch also finishes the bodies), then the hole mirror.  Returns the first HIP
+// error of the enqueued calls.
 template <typename Real>
 hipError_t enqueue_step(lb_ctx* c, hipStream_t s, int src_buf, const int64_t* step_ptr,
                         int64_t step_arg, bool capture)
@@ -459,10 +469,7 @@ hipError_t enqueue_step(lb_ctx* c, hipStream_t s, int src_buf, const int64_t* st
     hipError_t err = enqueue_couple<Real>(c, s, src_buf, step_ptr, step_arg, timed);
     const hipError_t e2 = enqueue_node<Real>(c, s, src_buf, step_ptr, step_arg, timed);
     if (err == hipSuccess) err = e2;
-    if (c->n_links > 0 && err == hipSuccess) {
-        launch_wall_links<Real>((Real*)c->f[src_buf ^ 1], c->d_links, c->n_links, s);
-        err = hipGetLastError();
-    }
+    if (err == hipSuccess) err = enqueue_links<Real>(c, s, c->f[src_buf ^ 1]);
     if (!c->hole_tiles.empty() && err == hipSuccess) {
         launch_mirror_holes<Real>((Real*)c->f[src_buf ^ 1], c->d_reps, c->d_rows, c->d_rowinfo,
                                   c->d_hole_tiles, (int32_t)c->hole_tiles.size(), c->hole, s);
@@ -613,15 +620,31 @@ int64_t links_without(const lb_ctx* c, int32_t replica)
     return n;
 }
 
-// concatenate the replicas' links (replica order) into the device list
-int upload_links(lb_ctx* c)
+// the replicas' links, concatenated in replica order, and each tile's range of them (the links
+// of a replica are sorted by slot, so by tile)
+std::vector<WallLink> collect_links(lb_ctx* c)
 {
     std::vector<WallLink> all;
     for (int r = 0; r < c->n_rep; ++r) {
-        c->rh[r].link0 = (int64_t)all.size();
-        all.insert(all.end(), c->rh[r].links.begin(), c->rh[r].links.end());
+        ReplicaHost& H = c->rh[r];
+        H.link0 = (int64_t)all.size();
+        all.insert(all.end(), H.links.begin(), H.links.end());
+        NodeTile* T = c->tiles[H.group].data() + H.tile0;
+        int64_t k = 0;
+        const int64_t n = (int64_t)H.links.size();
+        for (int32_t t = 0; t < H.n_tiles; ++t) {
+            T[t].link0 = H.link0 + k;
+            const int64_t k0 = k;
+            while (k < n && (H.links[k].g >> kPopBlockLog) == T[t].gt) ++k;
+            T[t].n_links = (int32_t)(k - k0);
+        }
     }
     c->n_links = (int64_t)all.size();
+    return all;
+}
+
+int upload_links(lb_ctx* c, const std::vector<WallLink>& all)
+{
     if (!all.empty()) {
         HIP_TRY(c, hipMemcpyAsync(c->d_links, all.data(), sizeof(WallLink) * all.size(),
                                   hipMemcpyHostToDevice, c->stream));
@@ -877,7 +900,7 @@ void enqueue_replay(lb_ctx* c, hipStream_t s, const void* src, void* dst, int64_
     for (int g = 0; g < 2; ++g)
         if (ag[g].n_tiles > 0)
             launch_node_step<Real>(ag[g], g == 1, c->n_beads > 0, nullptr, s);
-    if (c->n_links > 0) launch_wall_links<Real>(ag[0].dst, c->d_links, c->n_links, s);
+    (void)enqueue_links<Real>(c, s, dst);
     if (!c->hole_tiles.empty())
         launch_mirror_holes<Real>(ag[0].dst, c->d_reps, c->d_rows, c->d_rowinfo, c->d_hole_tiles,
                                   (int32_t)c->hole_tiles.size(), c->hole, s);
@@ -1391,8 +1414,9 @@ int lb_set_boundary_mask(lb_ctx* c, int32_t replica, const uint8_t* mask)
     H.links.swap(links);
     destroy_graphs(c);
     rebuild_tiles(c);
+    const std::vector<WallLink> all_links = collect_links(c);
     int rc = upload_tables(c);
-    if (rc == LB_OK) rc = upload_links(c);
+    if (rc == LB_OK) rc = upload_links(c, all_links);
     if (rc != LB_OK) return rc;
     // bodies already in this replica carry a copy of its geometry (no step has run yet, so
     // the host records are still the bodies' state)
@@ -1428,7 +1452,9 @@ int lb_set_wall_velocity(lb_ctx* c, int32_t replica, int32_t wall, const double 
     H.uwall.swap(uw);
     H.links.swap(links);
     destroy_graphs(c);
-    int rc = upload_links(c);
+    const std::vector<WallLink> all_links = collect_links(c);
+    int rc = upload_tables(c);   // the tiles' link ranges
+    if (rc == LB_OK) rc = upload_links(c, all_links);
     if (rc != LB_OK) return rc;
     return init_fluid(c, replica);
 }

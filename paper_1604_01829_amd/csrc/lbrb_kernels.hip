@@ -102,6 +102,22 @@ __device__ __forceinline__ void update_node(const StepArgs<Real>& a, const Repli
     }
 }
 
+// The moving-wall terms of a tile, added to slots that the tile's own threads have just stored.
+// Every thread of the workgroup calls it; n_links is uniform.  (Workgroups of several tiles leave
+// the links to a launch of their own: here they would cost that kernel registers, FP64 97 -> 111
+// with spills.)
+template <typename Real>
+__device__ __forceinline__ void add_tile_links(const StepArgs<Real>& a, const NodeTile& t)
+{
+    if (t.n_links == 0) return;
+    __syncthreads();
+    for (int k = threadIdx.x; k < t.n_links; k += kNodeBlock) {
+        const WallLink L = a.links[t.link0 + k];
+        Real* p = a.dst + pop_at(L.pop, L.g);
+        *p = *p + (Real)L.delta;
+    }
+}
+
 // What a bead record takes from its body besides the pose (uniform over the workgroup, read
 // once into registers).
 struct RecConst {
@@ -546,8 +562,9 @@ void node_step_kernel(const StepArgs<Real> a, const BodyArgs ba, int n_lead)
         int x, y, z;
         RowDesc self;
         locate_tile<MASKED>(R, a.rows, t, local, tile_rows, x, y, z, self);
-        if ((int)threadIdx.x >= t.count) return;
-        update_node<Real, MASKED, THERMAL, FORCES, NARROW, NT>(a, R, local, x, y, z, self, step);
+        if ((int)threadIdx.x < t.count)
+            update_node<Real, MASKED, THERMAL, FORCES, NARROW, NT>(a, R, local, x, y, z, self, step);
+        if constexpr (MASKED) add_tile_links<Real>(a, t);
     } else {
         const int first = xcd_tile(b, gridDim.x - n_lead) * PER;
         for (int q = 0; q < PER; ++q) {

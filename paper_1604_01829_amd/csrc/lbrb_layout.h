@@ -24,6 +24,7 @@
 #include <stdint.h>
 
 #include "lbrb_core.h"
+#include "lbrb_walls.h"
 
 namespace lbrb {
 
@@ -87,7 +88,8 @@ struct NodeTile {
     int64_t begin;          // local index of the first node
     int32_t row_lo, row_hi; // rows[] range that covers the tile (masked replicas)
     int32_t gt;             // global tile: (replica base + begin) / 256
-    int32_t pad;
+    int32_t n_links;        // moving-wall links of its nodes: links[link0 ... link0 + n_links)
+    int64_t link0;
 };
 
 struct DeviceHeader {
@@ -115,6 +117,7 @@ struct StepArgs {
     long long* gforce;      // fixed-point spread force, node-major (spread_stride words)
     uint8_t* flags;         // 1 byte per node: spread force present
     const uint8_t* hole;    // 1 byte per node: the wall id of a hole, 0 otherwise
+    const WallLink* links;  // moving-wall links (lbrb_walls.h), by tile
     CollideParams<Real> cp;
     Real gext[3];
     const int64_t* step_ptr;  // if set, step = *step_ptr + step_arg

@@ -265,3 +265,19 @@ def test_stokes_paper_channel():
           f"xi / (6 pi nu rho R) = {xi2 / stokes:.4f}", flush=True)
     assert abs(xi2 / xi1 - 1) < 1e-2
     assert xi2 > 0.8 * stokes and abs(F2[0]) < 1e-2 * F2[2] and abs(F2[1]) < 1e-2 * F2[2]
+
+
+@pytest.mark.parametrize("precision", ["f32", "f64"])
+def test_links_with_one_and_four_tiles_per_workgroup_agree_bitwise(precision):
+    """The node update applies its tile's links itself, or leaves them to a launch."""
+    import torch
+    wl = W.stokes_flow_workload(L=22, radius=3.0, U=1e-3, precision=precision)
+    out = []
+    for tiles in (1, 4):
+        sim = lbrb.simulation_from_workload(wl)
+        sim.set_tuning(tiles_per_wg=tiles)
+        sim.set_graph_steps(4)
+        sim.step(11)
+        out.append(sim.save_state())
+        sim.close()
+    assert torch.equal(out[0], out[1])
