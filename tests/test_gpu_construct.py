@@ -104,6 +104,30 @@ def test_thin_oblate_shell():
     _close(g, _oracle(axes, init, 600, C.DEFAULT_PARAMS), 1e-9, "thin oblate shell")
 
 
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 384, 385, 576, 577, 639, 640, 641, 1024, 1025])
+def test_closest_points_in_spare_waves(n):
+    """Shells up to 640 beads give the closest points waves of their own (one or two beads a
+    thread), larger ones do them with the pair forces.  The same operations in the same order:
+    bit for bit what the beads do in a shell of more than 640, its others out of their reach.
+    Sizes about the waves' ends, the second bead of a thread and the rule's line."""
+    R = math.sqrt(max(n, 4) / (4.0 * math.pi))
+    axes = (1.2 * R, 0.9 * R, R)
+    init = C.initial_shell(*axes, n, seed=n, jitter=0.05)
+    far = np.full((max(641 - n, 64), 3), 1e9) + 1e4 * np.arange(max(641 - n, 64))[:, None]
+    (one, both), (v1, v2) = C.relax_shells([axes] * 2, [init, np.concatenate([init, far])], FAST, 30)
+    np.testing.assert_array_equal(one, both[:n])
+    np.testing.assert_array_equal(v1, v2[:n])
+
+
+def test_crowded_shell_in_spare_waves():
+    """600 beads on a radius-2 sphere: most have more candidates than their 80 list entries and
+    walk all pairs, beside closest points in other waves."""
+    prm = dict(FAST, epsilon=1e-8)
+    init = C.initial_shell(2.0, 2.0, 2.0, 600, seed=6, jitter=0.01)
+    (g,), _ = C.relax_shells([(2.0, 2.0, 2.0)], [init], prm, 20)
+    _close(g, _oracle((2.0, 2.0, 2.0), init, 20, prm), 1e-12, "crowded 600 beads")
+
+
 def test_tetrahedron():
     rng = np.random.default_rng(1)
     u = rng.normal(size=(4, 3))
