@@ -72,7 +72,7 @@ __global__ __launch_bounds__(kNodeBlock) void adj_node_kernel(const AdjArgs<Real
     Real lF[3];
     collide_vjp<Real>(a.cp, d, F, lam, lF);
 #pragma unroll
-    for (int i = 0; i < Q; ++i) A.lam_cur[pop_at(i, g)] = lam[i];
+    for (int i = 0; i < Q; ++i) store_through(&A.lam_cur[pop_at(i, g)], lam[i]);
     if (flag) {
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) A.lamF[(int64_t)ax * a.N + g] = lF[ax];

@@ -40,9 +40,9 @@ void launch_timed(K kernel, dim3 grid, dim3 block, hipStream_t s, const LaunchEv
 // ------------------------------------------------------------------ node update
 
 // One fluid node: pull, add the force density (external, plus the spread force when the
-// node's flag is set and FORCES), collide with the node's noise, store (non-temporal stores
-// with NT: they bypass the caches, which pays once the population buffers are far larger than
-// the Infinity Cache and costs when they fit in it).
+// node's flag is set and FORCES), collide with the node's noise, store (written through the L2;
+// non-temporal with NT: they bypass the caches, which pays once the population buffers are far
+// larger than the Infinity Cache and costs when they fit in it).
 template <typename Real, bool MASKED, bool THERMAL, bool FORCES, bool NARROW, bool NT>
 __device__ __forceinline__ void update_node(const StepArgs<Real>& a, const ReplicaDesc& R,
                                             int64_t local, int x, int y, int z,
@@ -90,14 +90,14 @@ __device__ __forceinline__ void update_node(const StepArgs<Real>& a, const Repli
         for (int i = 0; i < Q; ++i) {
             Real* p = (Real*)(rb + pop_byte32<Real>((uint32_t)i, (uint32_t)local));
             if constexpr (NT) __builtin_nontemporal_store(d[i], p);
-            else *p = d[i];
+            else store_through(p, d[i]);
         }
     } else {
         Real* __restrict__ dst = a.dst;
 #pragma unroll
         for (int i = 0; i < Q; ++i) {
             if constexpr (NT) __builtin_nontemporal_store(d[i], &dst[pop_at(i, g)]);
-            else dst[pop_at(i, g)] = d[i];
+            else store_through(&dst[pop_at(i, g)], d[i]);
         }
     }
 }
