@@ -19,6 +19,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <cstddef>
 
 #include "lbrb_adjoint_device.h"
@@ -693,15 +694,16 @@ void launch_node_step(const StepArgs<Real>& a, bool masked, bool forces, const B
 // the 9 row descriptors around the corner node -> its 19 populations.  Within a workgroup
 // (32 beads) the stencil nodes are deduplicated through an LDS hash table keyed by node:
 // the first lane to claim a node pulls its populations once and publishes (drho, j); the
-// lanes' force contributions are summed as fixed-point words in LDS and the node's owner
-// adds each sum to the node with one device atomic per word.  Integer sums do not depend on
+// lanes' force contributions are summed as fixed-point words in LDS and the workgroup adds
+// each sum to the node with one device atomic per word.  Integer sums do not depend on
 // their order, so the result is the same as one atomic per lane.
 
 // LDS of one coupling workgroup: the node hash table, the nodes' moments and the force sums.
 // A workgroup's lanes claim at most kCoupleBlock distinct nodes, so kCoupleBlock slots always
-// suffice; FP32 takes twice that (shorter probes), FP64 takes kCoupleBlock so that its larger
-// entries leave room for 4 instead of 3 workgroups per CU (the batch's FP64 coupling 248 ->
-// 236 us).
+// suffice; FP32 takes twice that (shorter probes: 0.2 us of a small box's step), FP64 takes
+// kCoupleBlock so that its larger entries leave room for 4 instead of 3 workgroups per CU (the
+// batch's FP64 coupling 248 -> 236 us).
+constexpr int kAxisLanesFrom = 48;   // bead workgroups
 template <typename Real>
 struct CoupleLds {
     static constexpr int TS = (sizeof(Real) == 8 ? 1 : 2) * kCoupleBlock;   // power of two
@@ -862,14 +864,47 @@ __device__ __forceinline__ void couple_beads(const StepArgs<Real>& a, const Coup
         c.bead_torque[3 * bead + 2] = dv[0] * F[1] - dv[1] * F[0];
     }
     __syncthreads();
-    // one device atomic per node and word
-    if (owner) {
-        unsigned long long* gw = (unsigned long long*)(a.gforce + g * spread_stride<Real>());
-        for (int wd = 0; wd < NW; ++wd) {
-            const unsigned long long v = acc[wd][slot];
-            if (v != 0) atomicAdd(gw + wd, v);
+    // One device atomic per node and word.  The device's atomics bound a launch of many workgroups,
+    // and a node's words from one instruction are one request: four lanes take a node, one axis
+    // each, and the fourth sets the flag (an empty slot's sums are zero; all of a lane's slots are
+    // read before the first is used).  In FP32 a launch of few workgroups is bound by its latency,
+    // and the owner's three atomics, which need no walk over the slots, come sooner.  100 steps of
+    // n spheres of 201 beads (6.3 workgroups) in a 128^3 pore, owner / four lanes: FP32 n = 1 2.52 /
+    // 2.56 ms, 2 2.55 / 2.58, 6 2.59 / 2.60, 8 2.65 / 2.60, 12 2.71 / 2.62, 24 2.97 / 2.79; FP64
+    // n = 1 4.00 / 4.00, 2 4.02 / 4.00, 12 4.44 / 4.08, 24 4.97 / 4.31.
+    if (sizeof(Real) == 4 && ncb < kAxisLanesFrom) {
+        if (owner) {
+            unsigned long long* gw = (unsigned long long*)(a.gforce + g * spread_stride<Real>());
+            for (int wd = 0; wd < NW; ++wd) {
+                const unsigned long long v = acc[wd][slot];
+                if (v != 0) atomicAdd(gw + wd, v);
+            }
+            a.flags[g] = 1;
         }
-        a.flags[g] = 1;
+        return;
+    }
+    constexpr int NS = TS * 4 / kCoupleBlock, WA = NW / 3;
+    const int ax = threadIdx.x & 3, sl = threadIdx.x >> 2;
+    unsigned long long node[NS], sum[NS][WA];
+#pragma unroll
+    for (int k = 0; k < NS; ++k) {
+        node[k] = key[sl + k * (kCoupleBlock / 4)];
+#pragma unroll
+        for (int q = 0; q < WA; ++q)
+            sum[k][q] = ax < 3 ? acc[min(ax, 2) + 3 * q][sl + k * (kCoupleBlock / 4)] : 0;
+    }
+    if (ax < 3) {
+#pragma unroll
+        for (int k = 0; k < NS; ++k)
+#pragma unroll
+            for (int q = 0; q < WA; ++q)
+                if (sum[k][q] != 0)
+                    atomicAdd((unsigned long long*)(a.gforce + (int64_t)node[k] * spread_stride<Real>()) +
+                                  ax + 3 * q, sum[k][q]);
+    } else {
+#pragma unroll
+        for (int k = 0; k < NS; ++k)
+            if (node[k] != EMPTY) a.flags[node[k]] = 1;
     }
 }
 
@@ -879,22 +914,28 @@ __device__ __forceinline__ void couple_beads(const StepArgs<Real>& a, const Coup
 // Without it the kernel is compiled without that code (its registers stay those of the
 // coupling alone).  In FP32 the LDS admits 6 workgroups per CU; the coupling alone fits the
 // 80 registers of 6 waves per SIMD without spilling, so it is compiled for that occupancy.
+template <typename Real>
+union CoupleOrWcaLds {
+    CoupleLds<Real> couple;
+    WcaLds wca;
+};
+
 template <typename Real, bool WCA>
 __global__ __launch_bounds__(kCoupleBlock)
 __attribute__((amdgpu_waves_per_eu(sizeof(Real) == 4 && !WCA ? 6 : 1)))
 void couple_kernel(const StepArgs<Real> a, const CoupleArgs c, const BodyArgs ba, int n_wca)
 {
-    __shared__ CoupleLds<Real> L;
-    static_assert(sizeof(L) >= sizeof(WcaLds), "excluded-volume LDS fits in the coupling's");
+    __shared__ std::conditional_t<WCA, CoupleOrWcaLds<Real>, CoupleLds<Real>> L;
     if (WCA && (int)blockIdx.x < n_wca) {
         if ((int)blockIdx.x < ba.n_bodies) {
             const int64_t step = current_step(a.step_ptr, a.step_arg);
             wca_block(ba, blockIdx.x, (int)((step * ba.substeps + c.md_step) & 1),
-                      *reinterpret_cast<WcaLds*>(&L));
+                      reinterpret_cast<WcaLds&>(L));
         }
         return;
     }
-    couple_beads<Real>(a, c, blockIdx.x - n_wca, gridDim.x - n_wca, L);
+    couple_beads<Real>(a, c, blockIdx.x - n_wca, gridDim.x - n_wca,
+                       reinterpret_cast<CoupleLds<Real>&>(L));
 }
 
 template <typename Real>

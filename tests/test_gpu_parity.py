@@ -180,3 +180,29 @@ def test_pore_along_x_stored_in_x_rows(precision):
         else:
             _assert_close(e, 1e-5, 1e-6, 1e-6)
     gpu.close()
+
+
+@pytest.mark.parametrize("precision", ["f32", "f64"])
+@pytest.mark.parametrize("beads", [1504, 1505, 1536, 1537])
+def test_spread_by_owner_and_by_axis_lanes(precision, beads):
+    """47, 48 and 49 coupling workgroups (in FP32 the rule between the node owner's atomics and
+    four lanes per node): two replicas in one batch against each replica alone (10 and 38 or 39
+    workgroups), bit for bit, since the spread force is a sum of integers."""
+    reps = []
+    for k, n in enumerate((300, beads - 300)):
+        offs = W.sphere_beads(3.0 + 2.5 * k, n - 1)
+        m, inertia = W.solid_body_mass_inertia(1.0, 5.0, 5.0, 5.0)
+        body = W.body_record(offs, m, inertia, (9.3, 8.1, 10.7), vel=(1e-3, -2e-3, 5e-4),
+                             omega=(1e-4, 0.0, -2e-4), gamma=0.05)
+        assert len(offs) == n
+        reps.append(dict(shape=(20, 18, 22), seed=7 + k, mask=None, bodies=[body]))
+    wl = dict(name="two", precision=precision, steps=4, replicas=reps,
+              params=W.default_params(kT=4e-5, g_ext=(1e-6, 0.0, 2e-6)))
+    both = gpu_from_workload(wl)
+    both.step(4)
+    for r in (0, 1):
+        one = gpu_from_workload(dict(wl, replicas=[reps[r]]))
+        one.step(4)
+        np.testing.assert_array_equal(one.populations(0), both.populations(r))
+        np.testing.assert_array_equal(one.bead_forces(0, 0), both.bead_forces(r, 0))
+        assert np.abs(one.bead_forces(0, 0)).max() > 0.0
