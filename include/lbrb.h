@@ -296,9 +296,9 @@ int lb_kernel_times(lb_ctx* ctx, double* node_ms, int64_t* node_launches, double
 /* How the node update stores the populations.  LB_STORES_STREAMING: non-temporal stores,
  * which bypass the caches -- faster (3-5 % on MI355X) once the two population buffers are far
  * larger than the 256 MB Infinity Cache, much slower (about 25 %) when they fit in it.
- * LB_STORES_CACHED: ordinary stores.  LB_STORES_AUTO (default): the choice of lb_autotune
- * once it has run on this context, else streaming when the populations of the fluid nodes, in
- * both buffers, exceed 256 MiB.                                                            */
+ * LB_STORES_CACHED: stores through the L2s into that cache.  LB_STORES_AUTO (default): the
+ * choice of lb_autotune once it has run on this context, else streaming when the populations
+ * of the fluid nodes, in both buffers, exceed 256 MiB.                                     */
 #define LB_STORES_AUTO 0
 #define LB_STORES_CACHED 1
 #define LB_STORES_STREAMING 2
@@ -323,7 +323,8 @@ int lb_set_store_policy(lb_ctx* ctx, int32_t policy);
 typedef struct {
     int32_t tuned;            /* 1 once lb_autotune has run on this context                 */
     int32_t tiles_per_wg;     /* node tiles (256 nodes) per node-update workgroup           */
-    int32_t wg_per_cu;        /* cap on node-update workgroups per compute unit (0: none)   */
+    int32_t wg_per_cu;        /* cap on node-update workgroups per compute unit (0: none;
+                                 untuned: 5 in FP32 without masks while streaming, else 0)  */
     int32_t streaming;        /* 1: non-temporal population stores in use                   */
     int32_t candidates;       /* settings timed                                             */
     double node_us_default;   /* one node update of every tile with the untuned settings, us */

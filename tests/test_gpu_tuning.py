@@ -85,3 +85,20 @@ def test_tuning_arguments_are_checked():
         s.autotune(repeats=1001)
     assert e.value.code == lbrb.LB_ERR_ARG
     s.close()
+
+
+@pytest.mark.parametrize("precision,masked,cap", [("f32", False, 5), ("f32", True, 0),
+                                                  ("f64", False, 0)])
+def test_untuned_cap(precision, masked, cap):
+    """The untuned cap holds for FP32 boxes without masks while they stream, and changes nothing."""
+    wl = pore_batch() if masked else W.workload(1)
+    wl["precision"] = precision
+    a, b = gpu_from_workload(wl), gpu_from_workload(wl)
+    assert a.tuned_settings()["wg_per_cu"] == 0       # the populations fit in the cache
+    b.set_store_policy(lbrb.LB_STORES_STREAMING)
+    assert b.tuned_settings()["wg_per_cu"] == cap
+    a.step(12)
+    b.step(12)
+    assert np.array_equal(_state(a), _state(b))
+    a.close()
+    b.close()
