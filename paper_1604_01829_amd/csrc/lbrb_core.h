@@ -474,7 +474,10 @@ LBRB_HD void first_half(const double pos0[3], const double quat0[4], const doubl
     for (int a = 0; a < 3; ++a) pos[a] += dt * vel[a];
     const double wn = sqrt(omega[0] * omega[0] + omega[1] * omega[1] + omega[2] * omega[2]);
     if (wn > 0.0) {
-        const double h = hh * wn, s = sin(h) / wn, c = cos(h);
+        const double h = hh * wn;
+        double sh, c;
+        sincos(h, &sh, &c);
+        const double s = sh / wn;
         const double p[4] = {c, s * omega[0], s * omega[1], s * omega[2]};
         const double* q = quat;
         double n[4];
