@@ -384,44 +384,52 @@ void msd_kernel(const double* __restrict__ s, int n_frames, int n_comp, int n_la
         out[((int64_t)b * n_lags + tau - 1) * n_comp + comp] = v / (double)(n_frames - tau);
 }
 
-// theta^2 / (1 - cos theta) as a polynomial in y = 1 - cos theta on [0, 1]: interpolated at the
-// Chebyshev nodes from the series theta^2 = 2 sum_n (2 y)^n / (n^2 C(2n, n)) (that of the squared
-// arcsine of sqrt(y / 2)); relative error below 2e-17
-__device__ __forceinline__ double angle_poly(double y)
+// The squared angle from z = 1 - cos theta in [0, 1]: theta^2 = 2 z + z^2 r(z).  zl is what rounding
+// took from z (EXACT: nothing, as below 1/2): it enters with the slope 2 theta / sin theta (to 1.5 %).
+// r interpolates the series theta^2 = 2 sum_n (2 z)^n / (n^2 C(2n, n)) (that of the squared arcsine of
+// sqrt(z / 2)) at the Chebyshev nodes, theta^2 / z to a relative 2e-17.  With 2 z kept apart r's
+// rounding errors hardly reach the result.
+template <bool EXACT>
+__device__ __forceinline__ double squared_angle(double z, double zl)
 {
-    constexpr double c[20] = {0x1.0000000000000p+1, 0x1.55555555555f8p-2, 0x1.6c16c16c01aadp-4, 0x1.d41d41e56b008p-6,
-                               0x1.4ce19727a237cp-7, 0x1.f85e9253c495cp-9, 0x1.8ef8d0e792e25p-10, 0x1.47423977630aap-11,
-                               0x1.010ddcd930bd4p-12, 0x1.6dfbf751fe7a6p-13, -0x1.4e0a7b21d29e3p-13, 0x1.1ade30efbb8f1p-11,
-                               -0x1.03fce21011ae4p-10, 0x1.879e9e385f6dfp-10, -0x1.bbbdc34bad526p-10, 0x1.7bf11ffa6ad20p-10,
-                               -0x1.d8e9353bd632ep-11, 0x1.9717eb8ade077p-12, -0x1.b20de0c460ec2p-14, 0x1.b875556a46750p-17};
-    double v = c[20 - 1];
+    constexpr double c[19] = {0x1.55555555555f8p-2, 0x1.6c16c16c01aadp-4, 0x1.d41d41e56b008p-6, 0x1.4ce19727a237cp-7,
+                               0x1.f85e9253c495cp-9, 0x1.8ef8d0e792e25p-10, 0x1.47423977630aap-11, 0x1.010ddcd930bd4p-12,
+                               0x1.6dfbf751fe7a6p-13, -0x1.4e0a7b21d29e3p-13, 0x1.1ade30efbb8f1p-11, -0x1.03fce21011ae4p-10,
+                               0x1.879e9e385f6dfp-10, -0x1.bbbdc34bad526p-10, 0x1.7bf11ffa6ad20p-10, -0x1.d8e9353bd632ep-11,
+                               0x1.9717eb8ade077p-12, -0x1.b20de0c460ec2p-14, 0x1.b875556a46750p-17};
+    double r = c[19 - 1];
 #pragma unroll
-    for (int n = 20 - 2; n >= 0; --n) v = fma(v, y, c[n]);
-    return v;
+    for (int n = 19 - 2; n >= 0; --n) r = fma(r, z, c[n]);
+    return fma(2.0, z, EXACT ? z * z * r : fma(z * z, r, fma(fma(0.47, z, 2.0 / 3.0), z, 2.0) * zl));
 }
 
-// cos(theta / 2) = sqrt(1 - d / 2), d = 1 - cos theta in [0, 2]: the hardware's reciprocal square
-// root, two coupled Newton steps and a correction by the remainder (within an ulp)
-__device__ __forceinline__ double half_cosine(double d)
+// The same of half the angle, from its cosine c: cos(theta / 2) = sqrt((1 + c) / 2) by the hardware's
+// reciprocal square root, a coupled Newton step and a correction by the remainder; what is then
+// missing to the root, the rounding of 1 + c included, goes into zl.  (From 1 - c, which is rounded
+// to one bit less than an obtuse c, the squared angle lost up to six digits towards pi.)
+__device__ __forceinline__ double squared_half_angle(double c)
 {
-    const double x = fmax(fma(-0.5, d, 1.0), 1e-300);
-    const double r = __builtin_amdgcn_rsq(x);
-    double g = x * r, h = 0.5 * r;
-    double e = fma(-h, g, 0.5);
+    const double s = 1.0 + c, es = c - (s - 1.0);
+    const double x = fmax(0.5 * s, 1e-300);
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double e = fma(-h, g, 0.5);
     g = fma(g, e, g);
     h = fma(h, e, h);
-    e = fma(-h, g, 0.5);
-    g = fma(g, e, g);
-    return fma(fma(-g, g, x), h, g);
+    g = fma(fma(-g, g, x), h, g);
+    const double lo = fma(0.5, es, fma(-g, g, x)) * h, z = 1.0 - g;
+    return squared_angle<false>(z, ((1.0 - z) - g) - lo);
 }
 
 // grid (lag block, body): mean over origins of the squared angle between the reference
 // vectors.  The unit vectors R(q) r / |R(q) r| are computed once per staged frame; a thread's
 // origins are NT / LG apart, so that the lanes' reads are consecutive.  The squared angle is
 // analytic in the cosine at theta = 0, so it is a polynomial in 1 - cos theta up to a right
-// angle, and beyond from the half angle: with an arccosine and its square root per term 32
-// bodies, 20,000 frames and 1000 lags took 2135 us, this 1040 us.  A chunk with a
-// non-finite vector takes the arccosine itself, so that it propagates as before.  128 lags
+// angle, and beyond from the half angle, each wave by its widest angle: with an arccosine and its
+// square root per term 32 bodies, 20,000 frames and 1000 lags took 1968 us, this 784 us for steps of
+// 0.003 rad per frame, 991 us for 0.03, 1273 us for 0.3.  A term's r.m.s. error is 4e-17 to 6e-17 of it
+// at every angle, the squared arccosine's 4e-17 to 12e-17.  A chunk with a non-finite vector takes the
+// arccosine itself, so that it propagates as before.  128 lags
 // per workgroup where that fills the GPU (64 at twice the wavefronts: 1130 us), else 16.
 using WideAngles = LagShape<512, 16, 8>;
 using NarrowAngles = LagShape<256, 2, 8>;
@@ -487,22 +495,25 @@ void rotation_msd_kernel(const double* __restrict__ traj, int n_frames, int n_bo
 #pragma unroll
             for (int m = 0; m < M; ++m) d[m] = x0 * y[m][0] + x1 * y[m][1] + x2 * y[m][2];
             if (whole) {
-                bool wide = false;
+                bool wide = false, obtuse = false;
 #pragma unroll
                 for (int m = 0; m < M; ++m) {
-                    d[m] = fmin(fmax(1.0 - d[m], 0.0), 2.0);
-                    wide = wide || d[m] > 1.0;
+                    d[m] = fmin(fmax(d[m], -1.0), 1.0);
+                    wide = wide || d[m] < 0.5;
+                    obtuse = obtuse || d[m] < 0.0;
                 }
-                if (__any(wide)) {
+                if (!__any(wide)) {                         // 1 - c is exact
+#pragma unroll
+                    for (int m = 0; m < M; ++m) acc[m] += squared_angle<true>(1.0 - d[m], 0.0);
+                } else if (!__any(obtuse)) {
 #pragma unroll
                     for (int m = 0; m < M; ++m) {
-                        const bool far = d[m] > 1.0;
-                        const double z = far ? 1.0 - half_cosine(d[m]) : d[m];
-                        acc[m] += (far ? 4.0 : 1.0) * z * angle_poly(z);
+                        const double z = 1.0 - d[m];
+                        acc[m] += squared_angle<false>(z, (1.0 - z) - d[m]);
                     }
-                } else {
+                } else {                                    // beyond a right angle
 #pragma unroll
-                    for (int m = 0; m < M; ++m) acc[m] += d[m] * angle_poly(d[m]);
+                    for (int m = 0; m < M; ++m) acc[m] += 4.0 * squared_half_angle(d[m]);
                 }
             } else {
                 const int64_t t = t0 + o + lag0 + M * lg + 1;
