@@ -255,7 +255,70 @@ __global__ __launch_bounds__(kBlock) void add_before_kernel(double* __restrict__
 
 // ------------------------------------------------------------------ MSDs
 
-// The MSD kernels: one workgroup per block of consecutive lags and per body (and component).  A
+// Short trajectories: one workgroup per block of kLagBlock consecutive lags and per body.  The
+// origins are staged kChunk at a time in LDS together with the frames the block's lags reach from
+// them.  Thread (l, ph) accumulates lag lag0 + l + 1 over the origins t = ph mod 4 in increasing
+// order; the four phases are then added in a fixed order.  Every term reads its values from LDS,
+// but a workgroup starts and ends in 4 us, where the tiles below take 10 us however few frames
+// there are, and takes every component at once.
+constexpr int kLagBlock = 64;
+constexpr int kChunk = 256;
+constexpr int kPhases = kBlock / kLagBlock;
+static_assert(kPhases == 4, "four origin phases per lag");
+struct ShortMsd { static constexpr int lags = kLagBlock; };
+
+// stage frames f0 .. f0 + n - 1 of a body-major series (K values per frame) into T; frames
+// at or beyond n_frames read as zero
+template <int K>
+__device__ __forceinline__ void stage(const double* __restrict__ sb, int64_t f0, int n,
+                                      int n_frames, double (*T)[K])
+{
+    for (int e = threadIdx.x; e < n * K; e += kBlock) {
+        const int64_t f = f0 + e / K;
+        T[e / K][e % K] = f < n_frames ? sb[f * K + e % K] : 0.0;
+    }
+}
+
+// grid (lag block, body): mean over origins of the squared increment of each component
+template <int K>
+__global__ __launch_bounds__(kBlock) void short_msd_kernel(const double* __restrict__ s,
+                                                           int n_frames, int n_lags,
+                                                           double* __restrict__ out)
+{
+    __shared__ double A[kChunk][K];                       // origins t0 ..
+    __shared__ double Bt[kChunk + kLagBlock - 1][K];      // frames t0 + lag0 + 1 ..
+    __shared__ double part[kPhases][kLagBlock][K];
+    const int lag0 = blockIdx.x * kLagBlock, b = blockIdx.y;
+    const int l = threadIdx.x % kLagBlock, ph = threadIdx.x / kLagBlock;
+    const int tau = lag0 + l + 1;
+    const double* sb = s + (int64_t)b * n_frames * K;
+    double acc[K];
+    for (int k = 0; k < K; ++k) acc[k] = 0.0;
+    for (int64_t t0 = 0; t0 + lag0 + 1 < n_frames; t0 += kChunk) {
+        __syncthreads();
+        stage<K>(sb, t0, kChunk, n_frames, A);
+        stage<K>(sb, t0 + lag0 + 1, kChunk + kLagBlock - 1, n_frames, Bt);
+        __syncthreads();
+        // origins t0 + o with t0 + o + tau < n_frames; a counted loop, unrolled, lets the
+        // LDS reads of several origins be in flight together
+        const int o_end = (int)min<int64_t>(kChunk, n_frames - tau - t0);
+#pragma unroll 8
+        for (int o = ph; o < o_end; o += kPhases)
+            for (int k = 0; k < K; ++k) {
+                const double d = Bt[o + l][k] - A[o][k];
+                acc[k] += d * d;
+            }
+    }
+    for (int k = 0; k < K; ++k) part[ph][l][k] = acc[k];
+    __syncthreads();
+    if (ph == 0 && tau <= n_lags)
+        for (int k = 0; k < K; ++k) {
+            const double v = (part[0][l][k] + part[1][l][k]) + (part[2][l][k] + part[3][l][k]);
+            out[((int64_t)b * n_lags + tau - 1) * K + k] = v / (double)(n_frames - tau);
+        }
+}
+
+// Tiles: one workgroup per block of consecutive lags and per body (and component).  A
 // thread takes M consecutive lags by M origins of every chunk of origins; the chunk is staged in
 // LDS with the frames its lags reach, the next chunk's values being in flight to registers.  LG
 // groups of M lags by NT / LG sets of origins.  Every sum runs in a fixed order.
@@ -297,7 +360,8 @@ __device__ __forceinline__ double tile_total(double acc[S::tile], double (*part)
 // from registers: 2 FP64 operations per term against 0.18 LDS reads.  (One lag and one origin at
 // a time, every term read its two values from LDS; 8 x 8 tiles read 0.36 and took 220 us where
 // this takes 198.)  One pad value per M frames spreads the threads' reads over the banks.
-// 128 lags per workgroup where that fills the GPU (64 lags: 227 us, more staging), else 16.
+// 128 lags per workgroup, or 16 (64 lags: 227 us, more staging).  A tile that reaches past the last
+// frame goes frame by frame (term by term, each its two values from LDS, that took 14 us).
 // 32 bodies, 20,000 frames, 1000 lags: 3 components 569 -> 198 us, 6 components 809 ->
 // 395 us (at the FP64 vector rate: 97 and 195 us).
 using WideMsd = LagShape<256, 8, 16>;
@@ -367,15 +431,23 @@ void msd_kernel(const double* __restrict__ s, int n_frames, int n_comp, int n_la
                     acc[m] += d * d;
                 }
             }
-        } else if (left > 0) {
-#pragma unroll 1
-            for (int i = 0; i < M; ++i)
+        } else if (left > 0) {                              // frame by frame, up to the last
+            double x[M], y = w[0];
 #pragma unroll
-                for (int m = 0; m < M; ++m)
-                    if (i + m < left) {
-                        const double d = w[i + m + (i + m) / M] - a[i];
-                        acc[m] += d * d;
-                    }
+            for (int i = 0; i < M; ++i) x[i] = a[i];
+#pragma unroll
+            for (int j = 0; j < 2 * M - 1; ++j) {
+                const double yj = y;
+                if (j + 1 < 2 * M - 1) y = w[j + 1 + (j + 1) / M];
+                if (j < left) {
+#pragma unroll
+                    for (int m = 0; m < M; ++m)
+                        if (j - m >= 0 && j - m < M) {
+                            const double d = yj - x[j - m >= 0 && j - m < M ? j - m : 0];
+                            acc[m] += d * d;
+                        }
+                }
+            }
         }
     }
     const double v = tile_total<S>(acc, part);
@@ -767,7 +839,31 @@ void launch_cumulate(const double* traj, int32_t n_frames, int32_t n_bodies, dou
 }
 
 template <class S>
-int64_t lag_blocks(int32_t n_lags) { return (n_lags + S::lags - 1) / S::lags; }
+int64_t lag_blocks(int32_t n_lags) { return ((int64_t)n_lags + S::lags - 1) / S::lags; }
+
+// The MSD kernels' duration in us, for the choice between them: what one workgroup takes (start +
+// per_frame * frames: the latency of its chain) and what `blocks` of them cost the full GPU,
+// together as the root of the sum of squares.  Fitted to measured times (1 to 1024 bodies, 16 to
+// 8192 frames, 4 to 8191 lags; 1, 3 and 6 components), which it meets to 10 - 16 % r.m.s.
+struct MsdCost {
+    double start, per_frame;               // of one workgroup alone, us
+    double block_start, block_per_frame;   // of one among many, us
+
+    double us(double frames, int64_t blocks) const
+    {
+        return std::hypot(start + per_frame * frames, blocks * (block_start + block_per_frame * frames));
+    }
+};
+
+enum class MsdShape { Short, Narrow, Wide };
+
+// the short kernel where it is not estimated 10 % slower (it is left for a gain only), else the
+// faster tile
+MsdShape fastest(double t_short, double t_narrow, double t_wide)
+{
+    if (0.9 * t_short <= std::min(t_narrow, t_wide)) return MsdShape::Short;
+    return t_narrow <= t_wide ? MsdShape::Narrow : MsdShape::Wide;
+}
 
 template <int K, int ML>
 void launch_binned(const double* series, const double* radial, int32_t n_frames, int32_t n_bodies,
@@ -839,14 +935,34 @@ int lb_traj_msd(const double* series, int32_t n_frames, int32_t n_bodies, int32_
     if (!frames_ok(series, n_frames, n_bodies) || !out || k < 1 || k > 6 || n_lags < 1 ||
         n_lags >= n_frames || n_bodies > 65535)
         return LB_ERR_ARG;
-    if (lag_blocks<WideMsd>(n_lags) * n_bodies * k >= kFillBlocks)
-        hipLaunchKernelGGL((msd_kernel<WideMsd>), dim3(lag_blocks<WideMsd>(n_lags), n_bodies, k),
-                           dim3(WideMsd::threads), 0, (hipStream_t)stream, series, n_frames, k,
-                           n_lags, out);
-    else
+    hipStream_t s = (hipStream_t)stream;
+    const int64_t short_blocks = lag_blocks<ShortMsd>(n_lags) * n_bodies;
+    const int64_t narrow_blocks = lag_blocks<NarrowMsd>(n_lags) * n_bodies * k;
+    const int64_t wide_blocks = lag_blocks<WideMsd>(n_lags) * n_bodies * k;
+    switch (fastest(MsdCost{3.7, 0.0060, 0.0039, 1.0e-5}.us((double)n_frames * k, short_blocks),
+                    MsdCost{10.6, 0.0003, 0.037, 1.6e-6}.us(n_frames, narrow_blocks),
+                    MsdCost{9.9, 0.0032, 0.0104, 7.3e-6}.us(n_frames, wide_blocks))) {
+    case MsdShape::Short: {
+        const dim3 grid((unsigned)lag_blocks<ShortMsd>(n_lags), n_bodies);
+        switch (k) {
+        case 1: hipLaunchKernelGGL((short_msd_kernel<1>), grid, dim3(kBlock), 0, s, series, n_frames, n_lags, out); break;
+        case 2: hipLaunchKernelGGL((short_msd_kernel<2>), grid, dim3(kBlock), 0, s, series, n_frames, n_lags, out); break;
+        case 3: hipLaunchKernelGGL((short_msd_kernel<3>), grid, dim3(kBlock), 0, s, series, n_frames, n_lags, out); break;
+        case 4: hipLaunchKernelGGL((short_msd_kernel<4>), grid, dim3(kBlock), 0, s, series, n_frames, n_lags, out); break;
+        case 5: hipLaunchKernelGGL((short_msd_kernel<5>), grid, dim3(kBlock), 0, s, series, n_frames, n_lags, out); break;
+        default: hipLaunchKernelGGL((short_msd_kernel<6>), grid, dim3(kBlock), 0, s, series, n_frames, n_lags, out); break;
+        }
+        break;
+    }
+    case MsdShape::Narrow:
         hipLaunchKernelGGL((msd_kernel<NarrowMsd>), dim3(lag_blocks<NarrowMsd>(n_lags), n_bodies, k),
-                           dim3(NarrowMsd::threads), 0, (hipStream_t)stream, series, n_frames, k,
-                           n_lags, out);
+                           dim3(NarrowMsd::threads), 0, s, series, n_frames, k, n_lags, out);
+        break;
+    case MsdShape::Wide:
+        hipLaunchKernelGGL((msd_kernel<WideMsd>), dim3(lag_blocks<WideMsd>(n_lags), n_bodies, k),
+                           dim3(WideMsd::threads), 0, s, series, n_frames, k, n_lags, out);
+        break;
+    }
     return launched();
 }
 

@@ -217,3 +217,44 @@ def test_wide_angles_are_as_accurate_as_the_arccosine(lo, hi):
            for v in (got, np.arccos(c) ** 2)]
     print(f"{lo}-{hi} degrees: r.m.s. error {rms[0]:.3g}, the arccosine's {rms[1]:.3g}", flush=True)
     assert rms[0] <= 1.1 * rms[1]
+
+
+@pytest.mark.parametrize("n_frames,n_bodies,n_lags",
+                         [(1, 1, 0), (2, 1, 1), (257, 2, 65), (1536, 1, 17), (1537, 1, 1536), (4112, 1, 15),
+                          (1300, 40, 129), (700, 90, 257), (531, 40, 530)])
+def test_msd_short_narrow_and_wide(n_frames, n_bodies, n_lags):
+    """Every kernel of the MSD (by the estimates: the short one up to a few hundred frames, for one
+    component longer; 16 lags a workgroup for few bodies and lags; 128), at the ends of their blocks
+    and of the trajectory, for 1 to 6 components, against the oracle: both FP64 sums of up to 4112
+    terms in different orders, 1e-12 of the largest."""
+    rng = np.random.default_rng(n_frames + n_lags)
+    s = np.cumsum(rng.normal(size=(n_frames, n_bodies, 6)), axis=0)
+    for k in (1, 2, 3, 6):
+        if n_lags == 0:
+            with pytest.raises(lbrb.LBError):
+                GA.msd(_dev(s[:, :, :k].transpose(1, 0, 2)), 1)
+            continue
+        g = _host(GA.msd(_dev(s[:, :, :k].transpose(1, 0, 2)), n_lags))
+        o = OA.msd(s[:, :, :k], n_lags)
+        assert g.shape == o.shape
+        assert np.abs(g - o).max() <= 1e-12 * np.abs(o).max()
+
+
+@pytest.mark.parametrize("what,n_frames,n_bodies,n_lags,us", [("msd", 20, 20000, 10, 600), ("msd", 1000, 48, 300, 150)])
+def test_short_trajectories_take_no_tiles(what, n_frames, n_bodies, n_lags, us):
+    """Many bodies recorded a few times: blocks as long as a long trajectory's would be idle (2727 and
+    237 us for these; 60 and 27 us one lag per lane)."""
+    import torch
+    s = torch.randn(n_bodies, n_frames, 6 if n_frames == 20 else 3, dtype=torch.float64, device="cuda:0")
+    a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    best = 1e9
+    for _ in range(4):
+        GA.msd(s, n_lags)
+        a.record()
+        for _ in range(5):
+            GA.msd(s, n_lags)
+        b.record()
+        b.synchronize()
+        best = min(best, 1e3 * a.elapsed_time(b) / 5)
+    print(f"{what} {n_bodies} x {n_frames}, {n_lags} lags: {best:.1f} us", flush=True)
+    assert best <= us
