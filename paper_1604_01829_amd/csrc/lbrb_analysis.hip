@@ -456,6 +456,54 @@ void msd_kernel(const double* __restrict__ s, int n_frames, int n_comp, int n_la
         out[((int64_t)b * n_lags + tau - 1) * n_comp + comp] = v / (double)(n_frames - tau);
 }
 
+// Short trajectories, as short_msd_kernel: grid (lag block, body), mean over origins of the squared
+// angle between the reference vectors; the unit vectors R(q) r / |R(q) r| are computed once per
+// staged frame
+__global__ __launch_bounds__(kBlock) void short_rotation_kernel(const double* __restrict__ traj,
+                                                                int n_frames, int n_bodies,
+                                                                const double* __restrict__ ref,
+                                                                int n_lags, double* __restrict__ out)
+{
+    __shared__ double A[kChunk][3];
+    __shared__ double Bt[kChunk + kLagBlock - 1][3];
+    __shared__ double part[kPhases][kLagBlock];
+    const int lag0 = blockIdx.x * kLagBlock, b = blockIdx.y;
+    const int l = threadIdx.x % kLagBlock, ph = threadIdx.x / kLagBlock;
+    const int tau = lag0 + l + 1;
+    const double r[3] = {ref[3 * b], ref[3 * b + 1], ref[3 * b + 2]};
+    auto unit = [&](int64_t f, double* p) {
+        if (f >= n_frames) { p[0] = p[1] = p[2] = 0.0; return; }
+        double R[9];
+        rot_of(traj + 7 * (f * n_bodies + b) + 3, R);
+        for (int a = 0; a < 3; ++a) p[a] = R[3 * a] * r[0] + R[3 * a + 1] * r[1] + R[3 * a + 2] * r[2];
+        const double n = sqrt(p[0] * p[0] + p[1] * p[1] + p[2] * p[2]);
+        for (int a = 0; a < 3; ++a) p[a] /= n;
+    };
+    double acc = 0.0;
+    for (int64_t t0 = 0; t0 + lag0 + 1 < n_frames; t0 += kChunk) {
+        __syncthreads();
+        for (int e = threadIdx.x; e < kChunk; e += kBlock) unit(t0 + e, A[e]);
+        for (int e = threadIdx.x; e < kChunk + kLagBlock - 1; e += kBlock)
+            unit(t0 + lag0 + 1 + e, Bt[e]);
+        __syncthreads();
+        const int o_end = (int)min<int64_t>(kChunk, n_frames - tau - t0);
+#pragma unroll 8
+        for (int o = ph; o < o_end; o += kPhases) {
+            const double* p0 = A[o];
+            const double* p1 = Bt[o + l];
+            double c = p0[0] * p1[0] + p0[1] * p1[1] + p0[2] * p1[2];
+            c = c > 1.0 ? 1.0 : (c < -1.0 ? -1.0 : c);
+            const double th = acos(c);
+            acc += th * th;
+        }
+    }
+    part[ph][l] = acc;
+    __syncthreads();
+    if (ph == 0 && tau <= n_lags)
+        out[(int64_t)b * n_lags + tau - 1] =
+            ((part[0][l] + part[1][l]) + (part[2][l] + part[3][l])) / (double)(n_frames - tau);
+}
+
 // The squared angle from z = 1 - cos theta in [0, 1]: theta^2 = 2 z + z^2 r(z).  zl is what rounding
 // took from z (EXACT: nothing, as below 1/2): it enters with the slope 2 theta / sin theta (to 1.5 %).
 // r interpolates the series theta^2 = 2 sum_n (2 z)^n / (n^2 C(2n, n)) (that of the squared arcsine of
@@ -501,8 +549,8 @@ __device__ __forceinline__ double squared_half_angle(double c)
 // square root per term 32 bodies, 20,000 frames and 1000 lags took 1968 us, this 784 us for steps of
 // 0.003 rad per frame, 991 us for 0.03, 1273 us for 0.3.  A term's r.m.s. error is 4e-17 to 6e-17 of it
 // at every angle, the squared arccosine's 4e-17 to 12e-17.  A chunk with a non-finite vector takes the
-// arccosine itself, so that it propagates as before.  128 lags
-// per workgroup where that fills the GPU (64 at twice the wavefronts: 1130 us), else 16.
+// arccosine itself, so that it propagates as before.  128 lags per workgroup (64 at twice the
+// wavefronts: 1130 us where this took 1040), or 16.
 using WideAngles = LagShape<512, 16, 8>;
 using NarrowAngles = LagShape<256, 2, 8>;
 
@@ -857,11 +905,9 @@ struct MsdCost {
 
 enum class MsdShape { Short, Narrow, Wide };
 
-// the short kernel where it is not estimated 10 % slower (it is left for a gain only), else the
-// faster tile
 MsdShape fastest(double t_short, double t_narrow, double t_wide)
 {
-    if (0.9 * t_short <= std::min(t_narrow, t_wide)) return MsdShape::Short;
+    if (t_short <= std::min(t_narrow, t_wide)) return MsdShape::Short;
     return t_narrow <= t_wide ? MsdShape::Narrow : MsdShape::Wide;
 }
 
@@ -939,7 +985,9 @@ int lb_traj_msd(const double* series, int32_t n_frames, int32_t n_bodies, int32_
     const int64_t short_blocks = lag_blocks<ShortMsd>(n_lags) * n_bodies;
     const int64_t narrow_blocks = lag_blocks<NarrowMsd>(n_lags) * n_bodies * k;
     const int64_t wide_blocks = lag_blocks<WideMsd>(n_lags) * n_bodies * k;
-    switch (fastest(MsdCost{3.7, 0.0060, 0.0039, 1.0e-5}.us((double)n_frames * k, short_blocks),
+    // (the short kernel reads all components together; near the line it goes first, as the estimates
+    // of the tiles are low for one component)
+    switch (fastest(0.9 * MsdCost{3.7, 0.0060, 0.0039, 1.0e-5}.us((double)n_frames * k, short_blocks),
                     MsdCost{10.6, 0.0003, 0.037, 1.6e-6}.us(n_frames, narrow_blocks),
                     MsdCost{9.9, 0.0032, 0.0104, 7.3e-6}.us(n_frames, wide_blocks))) {
     case MsdShape::Short: {
@@ -972,15 +1020,29 @@ int lb_traj_rotation_msd(const double* traj, int32_t n_frames, int32_t n_bodies,
     if (!frames_ok(traj, n_frames, n_bodies) || !ref_body || !out || n_lags < 1 ||
         n_lags >= n_frames || n_bodies > 65535)
         return LB_ERR_ARG;
-    if (2 * lag_blocks<WideAngles>(n_lags) * n_bodies >= kFillBlocks)
-        hipLaunchKernelGGL((rotation_msd_kernel<WideAngles>),
-                           dim3(lag_blocks<WideAngles>(n_lags), n_bodies), dim3(WideAngles::threads),
-                           0, (hipStream_t)stream, traj, n_frames, n_bodies, ref_body, n_lags, out);
-    else
+    hipStream_t s = (hipStream_t)stream;
+    const int64_t short_blocks = lag_blocks<ShortMsd>(n_lags) * n_bodies;
+    const int64_t narrow_blocks = lag_blocks<NarrowAngles>(n_lags) * n_bodies;
+    const int64_t wide_blocks = lag_blocks<WideAngles>(n_lags) * n_bodies;
+    switch (fastest(MsdCost{5.5, 0.065, 0.005, 1.5e-4}.us(n_frames, short_blocks),
+                    MsdCost{11.7, 0.0117, 0.026, 2.7e-5}.us(n_frames, narrow_blocks),
+                    MsdCost{11.1, 0.044, 0.040, 1.65e-4}.us(n_frames, wide_blocks))) {
+    case MsdShape::Short:
+        hipLaunchKernelGGL(short_rotation_kernel, dim3(lag_blocks<ShortMsd>(n_lags), n_bodies),
+                           dim3(kBlock), 0, s, traj, n_frames, n_bodies, ref_body, n_lags, out);
+        break;
+    case MsdShape::Narrow:
         hipLaunchKernelGGL((rotation_msd_kernel<NarrowAngles>),
                            dim3(lag_blocks<NarrowAngles>(n_lags), n_bodies),
-                           dim3(NarrowAngles::threads), 0, (hipStream_t)stream, traj, n_frames,
-                           n_bodies, ref_body, n_lags, out);
+                           dim3(NarrowAngles::threads), 0, s, traj, n_frames, n_bodies, ref_body,
+                           n_lags, out);
+        break;
+    case MsdShape::Wide:
+        hipLaunchKernelGGL((rotation_msd_kernel<WideAngles>),
+                           dim3(lag_blocks<WideAngles>(n_lags), n_bodies), dim3(WideAngles::threads),
+                           0, s, traj, n_frames, n_bodies, ref_body, n_lags, out);
+        break;
+    }
     return launched();
 }
 

@@ -240,21 +240,46 @@ def test_msd_short_narrow_and_wide(n_frames, n_bodies, n_lags):
         assert np.abs(g - o).max() <= 1e-12 * np.abs(o).max()
 
 
-@pytest.mark.parametrize("what,n_frames,n_bodies,n_lags,us", [("msd", 20, 20000, 10, 600), ("msd", 1000, 48, 300, 150)])
+@pytest.mark.parametrize("what,n_frames,n_bodies,n_lags,us",
+                         [("msd", 20, 20000, 10, 600), ("msd", 1000, 48, 300, 150),
+                          ("rotation", 20, 20000, 10, 300)])
 def test_short_trajectories_take_no_tiles(what, n_frames, n_bodies, n_lags, us):
-    """Many bodies recorded a few times: blocks as long as a long trajectory's would be idle (2727 and
-    237 us for these; 60 and 27 us one lag per lane)."""
+    """Many bodies recorded a few times: blocks as long as a long trajectory's would be idle (2727,
+    237 and 681 us for these; 60, 27 and 96 us one lag per lane)."""
     import torch
-    s = torch.randn(n_bodies, n_frames, 6 if n_frames == 20 else 3, dtype=torch.float64, device="cuda:0")
+    if what == "msd":
+        s = torch.randn(n_bodies, n_frames, 6 if n_frames == 20 else 3, dtype=torch.float64,
+                        device="cuda:0")
+        run = lambda: GA.msd(s, n_lags)
+    else:
+        t = _dev(W.synthetic_trajectory(n_frames, n_bodies, seed=2))
+        ref = np.tile([1.0, 0.0, 0.0], (n_bodies, 1))
+        L, out = lbrb.library(), torch.empty(n_bodies * n_lags, dtype=torch.float64, device="cuda:0")
+        r = _dev(ref)
+        stream = torch.cuda.current_stream().cuda_stream
+        run = lambda: L.lb_traj_rotation_msd(t.data_ptr(), n_frames, n_bodies, r.data_ptr(), n_lags,
+                                             out.data_ptr(), stream)
     a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
     best = 1e9
     for _ in range(4):
-        GA.msd(s, n_lags)
+        run()
         a.record()
         for _ in range(5):
-            GA.msd(s, n_lags)
+            run()
         b.record()
         b.synchronize()
         best = min(best, 1e3 * a.elapsed_time(b) / 5)
     print(f"{what} {n_bodies} x {n_frames}, {n_lags} lags: {best:.1f} us", flush=True)
     assert best <= us
+
+
+@pytest.mark.parametrize("n_frames,n_bodies,n_lags",
+                         [(2, 1, 1), (65, 2, 64), (300, 1, 65), (1041, 1, 17), (1040, 3, 1039),
+                          (900, 120, 129), (257, 90, 256)])
+def test_rotation_short_narrow_and_wide(n_frames, n_bodies, n_lags):
+    """Every kernel of the rotational MSD at the ends of its blocks and of the trajectory, turning by
+    up to half a turn within it, against the oracle (1e-8, as above)."""
+    traj = W.synthetic_trajectory(n_frames, n_bodies, seed=n_frames + n_lags, rot_step=0.2)
+    ref = np.random.default_rng(n_lags).normal(size=(n_bodies, 3))
+    g, o = _host(GA.rotation_msd(_dev(traj), ref, n_lags)), OA.rotation_msd(traj, ref, n_lags)
+    _close(g, o, 1e-8, "rotation msd")
