@@ -21,6 +21,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "../../include/lbrb.h"
 #include "lbrb_analysis.h"
@@ -693,40 +694,66 @@ __global__ __launch_bounds__(kBlock) void binned_msd_kernel(const double* __rest
 // For at most kTileBins bins: grid (lag block, body, segment of origins).  A lane takes ML
 // consecutive lags and walks the origins of its wave's share of a chunk in order, so its ML
 // frames slide along (one new LDS value per origin and component, 2 ML FP64 operations) and the
-// origin is the same for the whole wave: its frame comes by scalar loads, and its bin is
-// uniform.  The running sums stay in registers while the bin does (a body crosses bin edges
-// rarely) and are added to the workgroup's LDS sums of that bin when it changes.  The reached
+// origin is the same for the whole wave: its frame comes by scalar loads a group of origins ahead,
+// and its bin is uniform.  The running sums stay in registers while the bin does (a body crosses bin
+// edges rarely) and are added to the workgroup's LDS sums of that bin when it changes.  The reached
 // frames are staged by their index modulo ML so that the lanes' reads are consecutive.  The sums
-// of bodies and segments are added to the outputs with device atomics, so their order (and the
+// of waves, bodies and segments are added with LDS and device atomics, so their order (and the
 // last bits of the sums) is not fixed; the counts are whole numbers and exact.  Segments: enough
 // workgroups to fill the GPU.
 // 32 bodies, 20,000 frames, 1000 lags, 8 bins: 1219 -> 300 us (one lag per lane: every
-// term read its frames from LDS and branched on its bin).
+// term read its frames from LDS and branched on its bin).  Past the last lag that an origin reaches
+// the terms are masked; added to the LDS sums one at a time, each origin's frame waited for, they
+// took 34 us of 32 bodies, 256 frames and 255 lags, now 29.
+//
+// ORDERED, for one or two bodies: the sums run in a fixed order, so that every call gives the same
+// bits (20,000 frames, 1000 lags, 8 bins: 76 us, in segments 41, by the kernel of one lag per lane
+// 1095).  Each wave has LDS sums of its own, added in order at the end, which leaves room for one
+// component and one lag per lane: the components are workgroups of their own along grid z, with
+// 16 waves in place of segments, and an origin's frame comes from the lane that loaded it.  At most
+// two of them add to one output, where the order does not matter: two bodies, or the halves of one
+// body's frames.
 constexpr int kTileBins = 8;
 constexpr int kBinBlock = 512;
-constexpr int kBinChunk = kBinBlock;             // origins staged at a time: 64 per wave
+constexpr int kOrderedBlock = 1024;
 constexpr int kGroup = 4;                        // origins between looks at their bins
 
-template <int K, int ML>
-__global__ __launch_bounds__(kBinBlock) __attribute__((amdgpu_waves_per_eu(4)))
+__device__ __forceinline__ double lane_value(double v, int lane)
+{
+    const unsigned long long u = __double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_readlane((unsigned)u, lane);
+    const unsigned hi = __builtin_amdgcn_readlane((unsigned)(u >> 32), lane);
+    return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+template <int K, int ML, bool ORDERED>
+__global__ __launch_bounds__(ORDERED ? kOrderedBlock : kBinBlock)
+__attribute__((amdgpu_waves_per_eu(4)))
 void binned_msd_tiled_kernel(
-    const double* __restrict__ s, const double* __restrict__ radial, int n_frames,
+    const double* __restrict__ s, const double* __restrict__ radial, int n_frames, int n_comp,
     const double* __restrict__ edges, int n_bins, int n_lags, int64_t segment,
     double* __restrict__ sums, double* __restrict__ counts)
 {
+    static_assert(!ORDERED || K == 1, "a component of its own");
+    static_assert(kGroup % ML == 0, "the window's offset is known within a group");
+    constexpr int NT = ORDERED ? kOrderedBlock : kBinBlock;
+    constexpr int chunk = NT;                    // origins staged at a time: 64 per wave
+    constexpr int copies = ORDERED ? NT / 64 : 1;
     constexpr int lags = 64 * ML;
-    constexpr int reach = kBinChunk + lags + ML;
+    constexpr int reach = chunk + lags + ML;
     __shared__ double Bt[K][ML][reach / ML];
-    __shared__ double total[kTileBins][ML][K][64];
+    __shared__ double total[copies][kTileBins][ML][K][64];
     __shared__ int count[kTileBins][ML][64];    // of the origins that not every lag reaches
     __shared__ int full[kTileBins];             // of the others
     const int lag0 = blockIdx.x * lags, b = blockIdx.y;
+    const int comp = ORDERED ? blockIdx.z % n_comp : 0, seg = ORDERED ? blockIdx.z / n_comp : blockIdx.z;
+    const int stride = ORDERED ? n_comp : K;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const double* __restrict__ sb = s + (int64_t)b * n_frames * K;
+    const double* __restrict__ sb = s + (int64_t)b * n_frames * stride + comp;
     const double* __restrict__ rb = radial + (int64_t)b * n_frames;
-    for (int e = threadIdx.x; e < kTileBins * ML * K * 64; e += kBinBlock) (&total[0][0][0][0])[e] = 0.0;
-    for (int e = threadIdx.x; e < kTileBins * ML * 64; e += kBinBlock) (&count[0][0][0])[e] = 0;
+    for (int e = threadIdx.x; e < copies * kTileBins * ML * K * 64; e += NT) (&total[0][0][0][0][0])[e] = 0.0;
+    for (int e = threadIdx.x; e < kTileBins * ML * 64; e += NT) (&count[0][0][0])[e] = 0;
     if (threadIdx.x < kTileBins) full[threadIdx.x] = 0;
     double acc[ML][K];
 #pragma unroll
@@ -737,29 +764,60 @@ void binned_msd_tiled_kernel(
         if (cur >= 0) {
 #pragma unroll
             for (int m = 0; m < ML; ++m)
-                for (int k = 0; k < K; ++k) atomicAdd(&total[cur][m][k][lane], acc[m][k]);
+                for (int k = 0; k < K; ++k) {
+                    if constexpr (ORDERED) total[wave][cur][m][k][lane] += acc[m][k];
+                    else atomicAdd(&total[0][cur][m][k][lane], acc[m][k]);
+                }
         }
 #pragma unroll
         for (int m = 0; m < ML; ++m)
             for (int k = 0; k < K; ++k) acc[m][k] = 0.0;
     };
-    const int64_t begin = segment * blockIdx.z;
+    double edge[kTileBins + 1];
+#pragma unroll
+    for (int q = 0; q <= kTileBins; ++q) edge[q] = q <= n_bins ? edges[q] : 0.0;
+    const int64_t begin = segment * seg;
     const int64_t end = begin + segment < n_frames ? begin + segment : n_frames;
-    for (int64_t t0 = begin; t0 < end && t0 + lag0 + 1 < n_frames; t0 += kBinChunk) {
+    // ORDERED: the frames that a chunk's lags reach, its origins' frames and their radial positions are
+    // loaded a chunk ahead
+    constexpr int NS = ORDERED ? (reach * K + NT - 1) / NT : 1;
+    double st[NS], rad = 0.0, org = 0.0;
+    auto load = [&](int64_t t0) {
+#pragma unroll
+        for (int q = 0; q < NS; ++q) {
+            const int e = threadIdx.x + q * NT;
+            const int64_t f = t0 + lag0 + 1 + e;
+            st[q] = e < reach && f < n_frames ? sb[f * stride] : 0.0;
+        }
+        const int64_t t = t0 + threadIdx.x;
+        rad = t < end ? rb[t] : 0.0;
+        org = t < end ? sb[t * stride] : 0.0;
+    };
+    if constexpr (ORDERED) load(begin);
+    for (int64_t t0 = begin; t0 < end && t0 + lag0 + 1 < n_frames; t0 += chunk) {
         __syncthreads();
-        for (int e = threadIdx.x; e < reach * K; e += kBinBlock) {
-            const int64_t f = t0 + lag0 + 1 + e / K;
-            Bt[e % K][e / K % ML][e / K / ML] = f < n_frames ? sb[f * K + e % K] : 0.0;
+        if constexpr (ORDERED) {
+#pragma unroll
+            for (int q = 0; q < NS; ++q)
+                if ((int)threadIdx.x + q * NT < reach) Bt[0][0][threadIdx.x + q * NT] = st[q];
+        } else {
+            for (int e = threadIdx.x; e < reach * K; e += NT) {
+                const int64_t f = t0 + lag0 + 1 + e / K;
+                Bt[e % K][e / K % ML][e / K / ML] = f < n_frames ? sb[f * stride + e % K] : 0.0;
+            }
         }
         __syncthreads();
         // the bin of each of the wave's 64 origins, one per lane (-1: none)
         const int64_t tw = t0 + 64 * wave;
         int bin = -1;
         if (tw + lane < end) {
-            const double rad = rb[tw + lane];
-            for (int q = 0; q < n_bins; ++q)
-                if (rad >= edges[q] && rad < edges[q + 1]) bin = q;
+            if constexpr (!ORDERED) rad = rb[tw + lane];
+#pragma unroll
+            for (int q = 0; q < kTileBins; ++q)
+                if (q < n_bins && rad >= edge[q] && rad < edge[q + 1]) bin = q;
         }
+        const double from = org;
+        if constexpr (ORDERED) load(t0 + chunk);
         // whether every origin reaches every lag: then an origin counts once for all of them
         const bool whole = tw + 64 <= end && tw + 63 + lag0 + lags < n_frames;
         if (whole)
@@ -767,50 +825,61 @@ void binned_msd_tiled_kernel(
                 const int c = __popcll(__ballot(bin == q));
                 if (c > 0 && lane == 0) atomicAdd(&full[q], c);
             }
+        // origins that some lag reaches
+        const int64_t some = (end < n_frames - 1 - lag0 ? end : n_frames - 1 - lag0) - tw;
+        const int n_org = some < 64 ? (int)some : 64;
         double w[ML][K];                        // the frames of the lane's lags
 #pragma unroll
         for (int m = 0; m < ML; ++m)
             for (int k = 0; k < K; ++k) w[m][k] = Bt[k][m][64 / ML * wave + lane];
-        // one origin, its frame in a: the lane's lags, then the window moves on
-        auto slide = [&](int o, int i) {
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-#pragma unroll
-                for (int m = 0; m + 1 < ML; ++m) w[m][k] = w[m + 1][k];
-                w[ML - 1][k] = Bt[k][i % ML][64 / ML * wave + o / ML + 1 + lane];
-            }
-        };
-        auto add = [&](const double a[K]) {
-#pragma unroll
-            for (int k = 0; k < K; ++k)
-#pragma unroll
-                for (int m = 0; m < ML; ++m) {
-                    const double d = w[m][k] - a[k];
-                    acc[m][k] += d * d;
-                }
-        };
-        if (whole) {
-            // the frames of a group of origins, loaded one group ahead
+        // the origins of the wave's share, a group at a time, their frames loaded one group ahead;
+        // MASK: not every lag reaches each
+        auto walk = [&](auto mask) {
+            constexpr bool MASK = decltype(mask)::value;
             double a[kGroup][K], next[kGroup][K];
             auto fetch = [&](int g) {
 #pragma unroll
                 for (int i = 0; i < kGroup; ++i)
-                    for (int k = 0; k < K; ++k) next[i][k] = sb[(tw + g + i) * K + k];   // uniform
+                    for (int k = 0; k < K; ++k) {
+                        if constexpr (ORDERED) {
+                            next[i][k] = lane_value(from, g + i);
+                        } else {                                                // uniform
+                            const int64_t t = tw + g + i;
+                            next[i][k] = sb[(!MASK || t < n_frames ? t : n_frames - 1) * K + k];
+                        }
+                    }
             };
+            // one origin: the lane's lags, then the window moves on
+            auto origin = [&](int g, int i) {
+                const int left = MASK ? (int)(n_frames - 1 - (tw + g + i) - lag0) - ML * lane : 0;
+#pragma unroll
+                for (int m = 0; m < ML; ++m) {
+                    const bool in = !MASK || m < left;
+                    for (int k = 0; k < K; ++k) {
+                        const double d = in ? w[m][k] - a[i][k] : 0.0;
+                        acc[m][k] += d * d;
+                    }
+                    if (MASK && in && cur >= 0) atomicAdd(&count[cur][m][lane], 1);
+                }
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+#pragma unroll
+                    for (int m = 0; m + 1 < ML; ++m) w[m][k] = w[m + 1][k];
+                    w[ML - 1][k] = Bt[k][i % ML][64 / ML * wave + (g + i) / ML + 1 + lane];
+                }
+            };
+            const int n = MASK ? n_org : 64;
             fetch(0);
 #pragma unroll 1
-            for (int g = 0; g < 64; g += kGroup) {
+            for (int g = 0; g < n; g += kGroup) {
 #pragma unroll
                 for (int i = 0; i < kGroup; ++i)
                     for (int k = 0; k < K; ++k) a[i][k] = next[i][k];
-                fetch(g + kGroup < 64 ? g + kGroup : 0);
+                fetch(g + kGroup < n ? g + kGroup : 0);
                 constexpr unsigned long long group = (1ull << kGroup) - 1;
                 if (((__ballot(bin == cur) >> g) & group) == group) {
 #pragma unroll
-                    for (int i = 0; i < kGroup; ++i) {
-                        add(a[i]);
-                        slide(g + i, i);
-                    }
+                    for (int i = 0; i < kGroup; ++i) origin(g, i);
                 } else {
 #pragma unroll
                     for (int i = 0; i < kGroup; ++i) {
@@ -819,48 +888,27 @@ void binned_msd_tiled_kernel(
                             flush();
                             cur = j;
                         }
-                        add(a[i]);
-                        slide(g + i, i);
+                        origin(g, i);
                     }
                 }
             }
-            continue;
-        }
-        // origins that not every lag reaches, or fewer than a wave's share
-        flush();
-        cur = -1;
-#pragma unroll 1
-        for (int g = 0; g < 64; g += ML) {
-            if (tw + g >= end || tw + g + lag0 + 1 >= n_frames) break;     // uniform
-#pragma unroll
-            for (int i = 0; i < ML; ++i) {
-                const int j = __builtin_amdgcn_readlane(bin, g + i);
-                const int64_t left = n_frames - 1 - (tw + g + i) - lag0 - ML * lane;
-                // (a scalar load may run for a wave whose lanes are all done: stay in bounds)
-                const int64_t t = tw + g + i < n_frames ? tw + g + i : n_frames - 1;
-                if (j >= 0) {
-#pragma unroll
-                    for (int m = 0; m < ML; ++m)
-                        if (m < left) {
-                            for (int k = 0; k < K; ++k) {
-                                const double d = w[m][k] - sb[t * K + k];
-                                atomicAdd(&total[j][m][k][lane], d * d);
-                            }
-                            atomicAdd(&count[j][m][lane], 1);
-                        }
-                }
-                slide(g + i, i);
-            }
-        }
+        };
+        if (whole) walk(std::false_type{});
+        else if (n_org > 0) walk(std::true_type{});
     }
     flush();
     __syncthreads();
-    for (int e = threadIdx.x; e < n_bins * lags * (K + 1); e += kBinBlock) {
+    for (int e = threadIdx.x; e < n_bins * lags * (K + 1); e += NT) {
         const int k = e % (K + 1), m = e / (K + 1) % lags, q = e / (K + 1) / lags;
         if (lag0 + m >= n_lags) continue;
         const int64_t o = (int64_t)q * n_lags + lag0 + m;
-        if (k < K) atomicAdd(sums + o * K + k, total[q][m % ML][k][m / ML]);
-        else atomicAdd(counts + o, (double)(full[q] + count[q][m % ML][m / ML]));
+        if (k < K) {
+            double v = 0.0;
+            for (int c = 0; c < copies; ++c) v += total[c][q][m % ML][k][m / ML];
+            atomicAdd(sums + o * stride + comp + k, v);
+        } else if (comp == 0) {
+            atomicAdd(counts + o, (double)(full[q] + count[q][m % ML][m / ML]));
+        }
     }
 }
 
@@ -917,12 +965,25 @@ void launch_binned(const double* series, const double* radial, int32_t n_frames,
                    double* counts, hipStream_t s)
 {
     // segments of origins: at least one chunk each, and no more workgroups than fill the GPU
-    const int64_t blocks = (n_lags + 64 * ML - 1) / (64 * ML);
-    const int64_t chunks = (n_frames + kBinChunk - 1) / kBinChunk;
+    const int64_t blocks = ((int64_t)n_lags + 64 * ML - 1) / (64 * ML);
+    const int64_t chunks = ((int64_t)n_frames + kBinBlock - 1) / kBinBlock;
     const int64_t per = std::max<int64_t>(1, chunks * blocks * n_bodies / kFillBlocks);
     const dim3 grid((unsigned)blocks, n_bodies, (unsigned)((chunks + per - 1) / per));
-    hipLaunchKernelGGL((binned_msd_tiled_kernel<K, ML>), grid, dim3(kBinBlock), 0, s, series, radial,
-                       n_frames, edges, n_bins, n_lags, per * kBinChunk, sums, counts);
+    hipLaunchKernelGGL((binned_msd_tiled_kernel<K, ML, false>), grid, dim3(kBinBlock), 0, s, series,
+                       radial, n_frames, K, edges, n_bins, n_lags, per * kBinBlock, sums, counts);
+}
+
+// one or two bodies: the frames of one body in two halves of whole chunks
+void launch_binned_ordered(const double* series, const double* radial, int32_t n_frames,
+                           int32_t n_bodies, int32_t k, const double* edges, int32_t n_bins,
+                           int32_t n_lags, double* sums, double* counts, hipStream_t s)
+{
+    const int64_t chunks = ((int64_t)n_frames + kOrderedBlock - 1) / kOrderedBlock;
+    const int64_t per = n_bodies == 1 ? (chunks + 1) / 2 : chunks;
+    const dim3 grid((unsigned)(((int64_t)n_lags + 63) / 64), n_bodies,
+                    (unsigned)(k * ((chunks + per - 1) / per)));
+    hipLaunchKernelGGL((binned_msd_tiled_kernel<1, 1, true>), grid, dim3(kOrderedBlock), 0, s, series,
+                       radial, n_frames, k, edges, n_bins, n_lags, per * kOrderedBlock, sums, counts);
 }
 
 bool frames_ok(const double* p, int32_t n_frames, int32_t n_bodies)
@@ -1058,8 +1119,11 @@ int lb_traj_binned_msd(const double* series, const double* radial, int32_t n_fra
         const int64_t n_sums = (int64_t)k * n_bins * n_lags, n_counts = (int64_t)n_bins * n_lags;
         hipLaunchKernelGGL(zero_sums_kernel, dim3((unsigned)((n_sums + n_counts + kBlock - 1) / kBlock)),
                            dim3(kBlock), 0, s, sums, n_sums, counts, n_counts);
-        // 256 lags per workgroup, or 64 where most of 256 would be past the last lag
-        if (n_lags > 128) {
+        // One or two bodies in a fixed order.  Else 256 lags per workgroup, or 64 where most of 256
+        // would be past the last lag.
+        if (n_bodies <= 2) {
+            launch_binned_ordered(series, radial, n_frames, n_bodies, k, edges, n_bins, n_lags, sums, counts, s);
+        } else if (n_lags > 128) {
             switch (k) {
             case 1: launch_binned<1, 4>(series, radial, n_frames, n_bodies, edges, n_bins, n_lags, sums, counts, s); break;
             case 2: launch_binned<2, 4>(series, radial, n_frames, n_bodies, edges, n_bins, n_lags, sums, counts, s); break;

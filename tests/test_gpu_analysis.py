@@ -283,3 +283,45 @@ def test_rotation_short_narrow_and_wide(n_frames, n_bodies, n_lags):
     ref = np.random.default_rng(n_lags).normal(size=(n_bodies, 3))
     g, o = _host(GA.rotation_msd(_dev(traj), ref, n_lags)), OA.rotation_msd(traj, ref, n_lags)
     _close(g, o, 1e-8, "rotation msd")
+
+
+@pytest.mark.parametrize("n_bodies", [1, 2])
+@pytest.mark.parametrize("n_frames,n_lags", [(5000, 300), (2100, 64), (130, 129)])
+def test_binned_msd_of_two_bodies_repeats_bit_for_bit(n_bodies, n_frames, n_lags):
+    """One or two bodies: the same bits on every call, for bins that change with every origin, and
+    the oracle's sums (up to 5000 terms in another order: 1e-12 of the largest)."""
+    rng = np.random.default_rng(n_frames + n_bodies)
+    series = np.cumsum(rng.normal(size=(n_frames, n_bodies, 3)), axis=0)
+    radial = rng.uniform(0.0, 10.0, size=(n_frames, n_bodies))
+    edges = [0.0, 1.0, 2.0, 3.5, 5.0, 6.0, 8.0, 9.0, 9.5]
+    s, r = _dev(series.transpose(1, 0, 2)), _dev(radial.T)
+    first, counts = (_host(x) for x in GA.binned_msd(s, r, edges, n_lags))
+    for _ in range(20):
+        again, c = GA.binned_msd(s, r, edges, n_lags)
+        np.testing.assert_array_equal(_host(again), first)
+        np.testing.assert_array_equal(_host(c), counts)
+    so, co = OA.binned_msd(series, radial, edges, n_lags)
+    np.testing.assert_array_equal(counts, co)
+    assert np.abs(first - so).max() <= 1e-12 * np.abs(so).max()
+
+
+@pytest.mark.parametrize("n_bodies,k,n_bins", [(1, 1, 8), (2, 2, 3), (3, 1, 1), (3, 2, 8), (5, 3, 2)])
+@pytest.mark.parametrize("n_frames,n_lags", [(2, 1), (65, 64), (66, 65), (513, 128), (512, 129), (1025, 511),
+                                             (2049, 1), (1300, 1299)])
+def test_binned_msd_edges(n_frames, n_lags, n_bodies, k, n_bins):
+    """Frames around a wave's 64 origins and the 512 or 1024 of a chunk, lags around a workgroup's 64
+    and 256, origins that no, some and every lag reaches; a non-finite frame reaches the sums of
+    its own origins and lags only."""
+    rng = np.random.default_rng(n_frames + n_lags + n_bodies)
+    series = np.cumsum(rng.normal(size=(n_frames, n_bodies, k)), axis=0)
+    radial = 5.0 + np.cumsum(rng.normal(size=(n_frames, n_bodies)), axis=0) / 10.0
+    edges = np.linspace(3.0, 7.0, n_bins + 1)
+    if n_frames > 600:
+        series[-40, 0, 0] = np.nan
+    g, c = (_host(x) for x in GA.binned_msd(_dev(series.transpose(1, 0, 2)), _dev(radial.T), edges,
+                                            n_lags))
+    so, co = OA.binned_msd(series, radial, edges, n_lags)
+    np.testing.assert_array_equal(c, co)
+    np.testing.assert_array_equal(np.isnan(g), np.isnan(so))
+    ok = ~np.isnan(so)
+    assert np.abs(g - so)[ok].max(initial=0.0) <= 1e-12 * np.abs(so[ok]).max(initial=1.0)
