@@ -242,15 +242,25 @@ def test_msd_short_narrow_and_wide(n_frames, n_bodies, n_lags):
 
 @pytest.mark.parametrize("what,n_frames,n_bodies,n_lags,us",
                          [("msd", 20, 20000, 10, 600), ("msd", 1000, 48, 300, 150),
-                          ("rotation", 20, 20000, 10, 300)])
+                          ("rotation", 20, 20000, 10, 300), ("binned", 256, 8, 255, 27)])
 def test_short_trajectories_take_no_tiles(what, n_frames, n_bodies, n_lags, us):
     """Many bodies recorded a few times: blocks as long as a long trajectory's would be idle (2727,
-    237 and 681 us for these; 60, 27 and 96 us one lag per lane)."""
+    237, 681 and 34 us for these; 60, 27, 96 and 22 us one lag per lane)."""
     import torch
     if what == "msd":
         s = torch.randn(n_bodies, n_frames, 6 if n_frames == 20 else 3, dtype=torch.float64,
                         device="cuda:0")
         run = lambda: GA.msd(s, n_lags)
+    elif what == "binned":
+        s = torch.randn(n_bodies, n_frames, 3, dtype=torch.float64, device="cuda:0")
+        rad = torch.rand(n_bodies, n_frames, dtype=torch.float64, device="cuda:0")
+        e = torch.linspace(0.0, 1.0, 5, dtype=torch.float64, device="cuda:0")
+        sums = torch.empty(4 * n_lags * 3, dtype=torch.float64, device="cuda:0")
+        counts = torch.empty(4 * n_lags, dtype=torch.float64, device="cuda:0")
+        L, stream = lbrb.library(), torch.cuda.current_stream().cuda_stream
+        run = lambda: L.lb_traj_binned_msd(s.data_ptr(), rad.data_ptr(), n_frames, n_bodies, 3,
+                                           e.data_ptr(), 4, n_lags, sums.data_ptr(),
+                                           counts.data_ptr(), stream)
     else:
         t = _dev(W.synthetic_trajectory(n_frames, n_bodies, seed=2))
         ref = np.tile([1.0, 0.0, 0.0], (n_bodies, 1))
