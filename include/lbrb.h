@@ -305,21 +305,21 @@ int lb_kernel_times(lb_ctx* ctx, double* node_ms, int64_t* node_launches, double
 int lb_set_store_policy(lb_ctx* ctx, int32_t policy);
 
 /* Launch settings of the node update, chosen by timing (not in the paper: a property of the
- * GPU).  lb_autotune times the context's own node kernel over its own tiles for every
- * combination of node tiles per workgroup (1 or 4; 256 nodes each), a cap on the node
- * workgroups resident per compute unit (none, 6, 5, 4; by dynamic LDS) and the store kind
- * (ordinary or non-temporal when both population buffers exceed the 256 MB Infinity Cache;
- * ordinary stores only when they fit in it, where the timed launches, which re-read an
- * unchanged buffer, cannot see what non-temporal stores cost the next step's reads; only the
- * forced kind under LB_STORES_CACHED/STREAMING): 16 or 8 settings.  It keeps the fastest
- * for the following steps if it beats the untuned settings by at least
- * 1 % (else the untuned ones).  The timed launches leave the simulation state
- * unchanged (no spread force is consumed, no body is finished; they write the buffer the next
- * step overwrites).  Results are kept for the process per (GPU architecture, precision,
- * thermal, tile counts, fluid nodes, store policy): repeats = 0 takes a kept result when there
- * is one and otherwise times 3 launches per setting; repeats > 0 always times that many and
- * replaces the kept result.  Synchronises the stream.  LB_ERR_ARG for repeats outside
- * 0..1000.  The choice changes no result, only speed.                                       */
+ * GPU).  lb_autotune times the context's own node kernel over its own tiles (and, where that
+ * leaves the moving-wall links to it, their launch) for every combination of node tiles per
+ * workgroup (1 or 4; 256 nodes each), a cap on the node workgroups resident per compute unit
+ * (none, 6, 5, 4; by dynamic LDS) and the store kind (cached or non-temporal when both
+ * population buffers exceed the 256 MB Infinity Cache; cached stores only when they fit in it,
+ * where the timed launches, which re-read an unchanged buffer, cannot see what non-temporal
+ * stores cost the next step's reads; only the forced kind under LB_STORES_CACHED/STREAMING):
+ * 16 or 8 settings.  It keeps the fastest for the following steps if it beats the untuned
+ * settings by at least 1 % (else the untuned ones).  The timed launches leave the simulation
+ * state unchanged (no spread force is consumed, no body is finished; they write the buffer the
+ * next step overwrites).  Results are kept for the process per (GPU architecture, precision,
+ * thermal, tile counts, fluid nodes, moving-wall links, store policy): repeats = 0 takes a kept
+ * result when there is one and otherwise times 3 launches per setting; repeats > 0 always times
+ * that many and replaces the kept result.  Synchronises the stream.  LB_ERR_ARG for repeats
+ * outside 0..1000.  The choice changes no result, only speed.                              */
 typedef struct {
     int32_t tuned;            /* 1 once lb_autotune has run on this context                 */
     int32_t tiles_per_wg;     /* node tiles (256 nodes) per node-update workgroup           */

@@ -1126,10 +1126,13 @@ int run_adjoint(lb_ctx* c, int32_t T, int32_t K, char* ws, const AdjPlan& ap)
 // resident per CU (by dynamic LDS), ordinary or non-temporal population stores -- are timed on
 // the context's own node kernel over its own tiles: every tile group, the kernel the steps
 // launch (with the force path when the context has beads) but without body finishing, pulling
-// from the current buffer and writing the other one, which the next step overwrites whole.
+// from the current buffer and writing the other one, which the next step overwrites whole.  With
+// moving walls their links are timed too: one tile per workgroup adds them in the node update,
+// several leave them to a launch of their own in every step.
 // Between steps every spread force has been consumed (flags and words are zero), so the timed
 // launches take none and the simulation state is unchanged.  Results are kept per
-// (device architecture, precision, thermal, tile counts, fluid nodes) for the process.
+// (device architecture, precision, thermal, tile counts, fluid nodes, moving-wall links, store
+// policy) for the process.
 
 struct TuneCand { int32_t per, cap, streaming; };
 constexpr double kTuneMargin = 0.01;   // a setting must beat the untuned one by this fraction
@@ -1148,26 +1151,30 @@ std::string tune_key(const lb_ctx* c)
     for (int r = 0; r < c->n_rep; ++r) fluid += c->reps[r].n_fluid;
     return arch + "|" + std::to_string(c->p.precision) + "|" + std::to_string(c->p.kT > 0.0) + "|" +
            std::to_string(c->tiles[0].size()) + "|" + std::to_string(c->tiles[1].size()) + "|" +
-           std::to_string(fluid) + "|" + std::to_string(c->store_policy);
+           std::to_string(fluid) + "|" + std::to_string(c->n_links) + "|" +
+           std::to_string(c->store_policy);
 }
 
-// mean duration (us) of one node update of every tile group with the context's current settings
+// mean duration (us) of one node update of every tile group, the moving-wall links included, with the
+// context's current settings
 template <typename Real>
 int time_node_update(lb_ctx* c, hipEvent_t e0, hipEvent_t e1, int reps, double& us)
 {
     StepArgs<Real> ag[2] = {step_args<Real>(c, 0, c->cur), step_args<Real>(c, 1, c->cur)};
     auto once = [&]() {
+        hipError_t err = hipSuccess;
         for (int g = 0; g < 2; ++g)
-            if (ag[g].n_tiles > 0)
+            if (ag[g].n_tiles > 0 && err == hipSuccess) {
                 launch_node_step<Real>(ag[g], g == 1, c->n_beads > 0, nullptr, c->stream);
+                err = hipGetLastError();
+            }
+        return err == hipSuccess ? enqueue_links<Real>(c, c->stream, c->f[c->cur ^ 1]) : err;
     };
-    once();   // warm-up
-    HIP_TRY(c, hipGetLastError());
+    HIP_TRY(c, once());   // warm-up
     HIP_TRY(c, hipEventRecord(e0, c->stream));
-    for (int k = 0; k < reps; ++k) once();
+    for (int k = 0; k < reps; ++k) HIP_TRY(c, once());
     HIP_TRY(c, hipEventRecord(e1, c->stream));
     HIP_TRY(c, hipEventSynchronize(e1));
-    HIP_TRY(c, hipGetLastError());
     float ms = 0.0f;
     HIP_TRY(c, hipEventElapsedTime(&ms, e0, e1));
     us = 1e3 * (double)ms / reps;
