@@ -899,9 +899,9 @@ void enqueue_recoupling(lb_ctx* c, hipStream_t s, const StepArgs<Real>& a, int64
 
 // forward step without finishing the bodies, src -> dst.  Fixed bodies with one MD step: the
 // records hold the only pose; otherwise the couplings are recomputed from the stored body
-// table `bodies` of the step (enqueue_recoupling).
+// table `bodies` of the step (enqueue_recoupling).  Returns the first HIP error.
 template <typename Real>
-void enqueue_replay(lb_ctx* c, hipStream_t s, const void* src, void* dst, int64_t step,
+hipError_t enqueue_replay(lb_ctx* c, hipStream_t s, const void* src, void* dst, int64_t step,
                     const Body* bodies, Body* scr, double* bf, size_t nbf)
 {
     StepArgs<Real> ag[2] = {step_args_on<Real>(c, 0, src, dst), step_args_on<Real>(c, 1, src, dst)};
@@ -913,10 +913,14 @@ void enqueue_replay(lb_ctx* c, hipStream_t s, const void* src, void* dst, int64_
     for (int g = 0; g < 2; ++g)
         if (ag[g].n_tiles > 0)
             launch_node_step<Real>(ag[g], g == 1, c->n_beads > 0, nullptr, s);
-    (void)enqueue_links<Real>(c, s, dst);
-    if (!c->hole_tiles.empty())
+    hipError_t err = hipGetLastError();
+    if (err == hipSuccess) err = enqueue_links<Real>(c, s, dst);
+    if (!c->hole_tiles.empty() && err == hipSuccess) {
         launch_mirror_holes<Real>(ag[0].dst, c->d_reps, c->d_rows, c->d_rowinfo, c->d_hole_tiles,
                                   (int32_t)c->hole_tiles.size(), c->hole, s);
+        err = hipGetLastError();
+    }
+    return err;
 }
 
 // one reverse step at forward step `step` (index n of the window), forward state pulled from
@@ -1090,11 +1094,10 @@ int run_adjoint(lb_ctx* c, int32_t T, int32_t K, char* ws, const AdjPlan& ap)
         const int32_t n0 = sg * K, n1 = std::min(T, n0 + K);
         auto state = [&](int32_t j) { return j == 0 ? ck(sg) : seg(j - 1); };
         for (int32_t j = 0; j + 1 < n1 - n0; ++j)
-            enqueue_replay<Real>(c, s, state(j), state(j + 1), step0 + n0 + j,
-                                 fb ? snap + (size_t)c->n_bodies * (n0 + j) : nullptr,
-                                 (Body*)(ws + ap.off_scr), (double*)(ws + ap.off_bf),
-                                 3 * (size_t)std::max<int32_t>(c->n_beads, 1));
-        HIP_TRY(c, hipGetLastError());
+            HIP_TRY(c, enqueue_replay<Real>(c, s, state(j), state(j + 1), step0 + n0 + j,
+                                            fb ? snap + (size_t)c->n_bodies * (n0 + j) : nullptr,
+                                            (Body*)(ws + ap.off_scr), (double*)(ws + ap.off_bf),
+                                            3 * (size_t)std::max<int32_t>(c->n_beads, 1)));
         for (int32_t n = n1 - 1; n >= n0; --n) {
             // the coupling of step n - 1 joins this step's bead launch when its state is at
             // hand and nothing in between rewrites the force accumulators: inside a segment,

@@ -36,3 +36,7 @@ def _run(exe, what):
 
 def test_autotuner_times_the_moving_wall_links(api_check):
     _run(api_check, "tune")
+
+
+def test_a_failing_launch_of_a_replay_is_reported(api_check):
+    _run(api_check, "replay")
