@@ -20,8 +20,10 @@
  *
  * Memory and streams.  The library never allocates device memory for its state: the caller
  * passes one device workspace of lb_workspace_bytes() bytes (for instance a torch tensor)
- * and a HIP stream; the workspace must outlive the context.  Every call enqueues work on
- * that stream.  lb_observables, lb_save_state, lb_load_state, lb_set_boundary_mask and
+ * and a HIP stream; the workspace must outlive the context.  lb_init also allocates the pinned
+ * host memory that lb_observables answers through (64 bytes and 160 per body of max_bodies;
+ * LB_ERR_HIP if there is none), which lb_destroy frees.  Every call enqueues work on that
+ * stream.  lb_observables, lb_save_state, lb_load_state, lb_set_boundary_mask and
  * rb_add_raspberry synchronise the stream before returning; lb_rb_step does not.
  *
  * Errors.  Every call returns LB_OK (0) or a negative code; lb_last_error() gives a message.

@@ -230,7 +230,6 @@ struct lb_ctx {
     hipGraphExec_t gexec[2] = {nullptr, nullptr};
     hipStream_t cap_stream = nullptr;
     double* host_out = nullptr;       // pinned: the answer of lb_observables
-    size_t host_words = 0;
     // timing
     bool timing = false;
     int32_t store_policy = LB_STORES_AUTO;
@@ -1346,6 +1345,12 @@ int lb_init(const lb_params* params, const lb_replica* replicas, int32_t n_repli
         e = hipMemsetAsync(c->f[k], 0, real * Q * pl.N, c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->flags, 0, pl.N, c->stream);
     if (e == hipSuccess) e = hipMemsetAsync(c->hole, 0, pl.N, c->stream);
+    // pinned host memory for the answer of lb_observables (a device-to-host copy of pageable memory per
+    // array took 20-35 us each, three of them per reading; the allocation takes about 15 us, once)
+    if (e == hipSuccess)
+        e = hipHostMalloc((void**)&c->host_out,
+                          sizeof(double) * (8 + (size_t)kObserveBodyWords * (size_t)pl.body_cap),
+                          hipHostMallocDefault);
     if (e != hipSuccess) { lb_destroy(c); return LB_ERR_HIP; }
     int rc = upload_tables(c);
     if (rc == LB_OK) rc = init_fluid(c, -1);
@@ -1666,20 +1671,6 @@ int lb_observables(lb_ctx* c, int32_t replica, lb_totals* out, rb_state* bodies,
     if (!check_replica(c, replica)) return LB_ERR_ARG;
     const ReplicaDesc& R = c->reps[replica];
     const ReplicaHost& H = c->rh[replica];
-    // pinned host memory for the answer, grown with the bodies (a device-to-host copy of pageable
-    // memory per array took 20-35 us each, three of them per call)
-    const size_t need = 8 + (size_t)kObserveBodyWords * (size_t)c->n_bodies;
-    if (c->host_words < need) {
-        if (c->host_out) {
-            HIP_TRY(c, hipStreamSynchronize(c->stream));
-            HIP_TRY(c, hipHostFree(c->host_out));
-            c->host_out = nullptr;
-            c->host_words = 0;
-        }
-        const size_t words = std::max(need, 8 + (size_t)kObserveBodyWords * 64);
-        HIP_TRY(c, hipHostMalloc((void**)&c->host_out, sizeof(double) * words, hipHostMallocDefault));
-        c->host_words = words;
-    }
     const ObserveOut host{c->host_out, c->host_out + 8};
     if (is_f32(c)) {
         StepArgs<float> a = step_args<float>(c, H.group, c->cur);

@@ -40,3 +40,7 @@ def test_autotuner_times_the_moving_wall_links(api_check):
 
 def test_a_failing_launch_of_a_replay_is_reported(api_check):
     _run(api_check, "replay")
+
+
+def test_observables_allocate_nothing(api_check):
+    _run(api_check, "observe")
