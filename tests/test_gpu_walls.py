@@ -281,3 +281,37 @@ def test_links_with_one_and_four_tiles_per_workgroup_agree_bitwise(precision):
         out.append(sim.save_state())
         sim.close()
     assert torch.equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("precision", ["f32", "f64"])
+@pytest.mark.parametrize("policy", [lbrb.LB_STORES_CACHED, lbrb.LB_STORES_STREAMING])
+@pytest.mark.parametrize("holes", [False, True])
+def test_links_after_either_store_and_before_the_mirror(holes, policy, precision):
+    """The links that the node update adds to slots its workgroup has just stored, through the L2 or
+    past it, against the launch after the update, bit for bit; and with a moving block between the
+    fluid runs of a row, whose holes take the reflected populations with the links' terms in them."""
+    import torch
+    out = []
+    for tiles in (1, 4):
+        wl = walls_case(precision, 4e-5)
+        if holes:
+            wl["replicas"][0]["mask"][6:8, 2:4, 7:9] = 2
+        sim = lbrb.simulation_from_workload(wl)
+        sim.set_store_policy(policy)
+        sim.set_tuning(tiles_per_wg=tiles)
+        sim.set_graph_steps(4)
+        sim.step(11)
+        assert sim.tuned_settings()["streaming_stores"] == (policy == lbrb.LB_STORES_STREAMING)
+        out.append((sim.save_state(), sim.populations()))
+        sim.close()
+    assert torch.equal(out[0][0], out[1][0])
+    np.testing.assert_array_equal(out[0][1], out[1][1])
+    orc = oracle_from_workload(wl)
+    orc.step(11)
+    gpu = lbrb.simulation_from_workload(wl)
+    gpu.set_store_policy(policy)
+    gpu.step(11)
+    e = compare(gpu, orc)
+    _print("links", e)
+    _assert_close(e, *_tol(precision))
+    gpu.close()
