@@ -53,11 +53,7 @@ __device__ __forceinline__ void adj_bead_lanes(const AdjArgs<Real>& A, int tid)
     if constexpr (FREE) {
         const Body& Bd = A.snap[body];
         const Pose& P = Bd.pose[A.pose_par];
-        const double* off = A.beads[bead].off;
-        for (int ax = 0; ax < 3; ++ax) {
-            arm[ax] = P.rot[3 * ax] * off[0] + P.rot[3 * ax + 1] * off[1] + P.rot[3 * ax + 2] * off[2];
-            r[ax] = P.pos[ax] + arm[ax];
-        }
+        place_bead(P, A.beads[bead].off, arm, r);
         if (Bd.fixed) {
             vel[0] = vel[1] = vel[2] = 0.0;
         } else {

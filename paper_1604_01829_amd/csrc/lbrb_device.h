@@ -157,6 +157,20 @@ __device__ __forceinline__ Real load_pop(const Real* __restrict__ src, int64_t b
     }
 }
 
+// A bead's arm r - R and position from its body's pose and its offset.  The reverse pass's bead pass
+// calls it again for the pose that a step's records were written from, and reads the force adjoint at
+// the nodes of that position's stencil, where it is stored only at the nodes that the coupling reached
+// from the records: the two have to agree bit for bit, so there is one function, and sums of
+// products are fused within an expression only (-ffp-contract=on), alike wherever it is inlined.
+template <typename PoseT>
+__device__ __forceinline__ void place_bead(const PoseT& P, const double off[3], double arm[3], double r[3])
+{
+    for (int ax = 0; ax < 3; ++ax) {
+        arm[ax] = P.rot[3 * ax] * off[0] + P.rot[3 * ax + 1] * off[1] + P.rot[3 * ax + 2] * off[2];
+        r[ax] = P.pos[ax] + arm[ax];
+    }
+}
+
 // A population store that writes through the XCD's L2 (agent scope).  A plain store leaves the
 // line dirty, and the end of the kernel waits until each L2 has written its dirty lines back: 3 us
 // after the node update of a box larger than the L2s, during which nothing else runs.  Written

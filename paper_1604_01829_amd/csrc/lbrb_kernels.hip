@@ -171,10 +171,7 @@ __device__ __forceinline__ void write_bead_pose(const PoseT& P, bool fixed, cons
     static_assert(offsetof(BeadRec, r) == 0 && offsetof(BeadRec, dv) == 24 &&
                   offsetof(BeadRec, v) == 48, "position, arm and velocity lead the record");
     double dv[3], v[3];
-    for (int ax = 0; ax < 3; ++ax) {
-        dv[ax] = P.rot[3 * ax] * off[0] + P.rot[3 * ax + 1] * off[1] + P.rot[3 * ax + 2] * off[2];
-        r[ax] = P.pos[ax] + dv[ax];
-    }
+    place_bead(P, off, dv, r);
     if (fixed) {
         v[0] = v[1] = v[2] = 0.0;
     } else {

@@ -841,3 +841,32 @@ def test_gamma_calibrated_to_a_hydrodynamic_radius():
     assert abs(radii[64] - target) <= 1e-8 * target
     for L in (48, 80):
         assert abs(radii[L] - target) <= 0.02 * target
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("masked,md,free", [(False, 1, False), (False, 1, True), (True, 1, True), (False, 2, True)])
+def test_reverse_pass_reads_nothing_it_has_not_written(masked, md, free, precision):
+    """The workspace filled with NaN or with zeros: the force adjoint is stored only at the nodes that
+    the coupling reached, and the bead pass, which forms the positions again, reads only those --
+    beads on cell faces among them.  FP64 to 1e-12, FP32 to 1e-6 (the sampled velocities' adjoints
+    are added by atomics)."""
+    from paper_1604_01829_amd import lbrb
+    import torch
+    shape, mask, pp, bodies = _free_case(masked) if free else _case(masked)
+    faces = 0.5 * np.array([[i, j, k] for i in (-1, 0, 2) for j in (-2, 1) for k in (0, 3)], float)
+    bodies = [(faces, np.array([6.0, 6.5, 5.0]), np.array([1.0, 0, 0, 0]), bodies[0][3]), bodies[1]]
+    T, K = 7, 3
+    a = _weights(T, 2)
+    out = []
+    for fill in (0x00, 0xFF):
+        sim = _gpu_free(shape, mask, pp, bodies, precision, md) if free else _gpu(shape, mask, pp, bodies, precision)
+        n = lbrb.lb_adjoint_workspace_bytes(sim.ctx, T, K)
+        ws = torch.full((n + 256,), fill, dtype=torch.uint8, device="cuda:0")
+        at = (ws.data_ptr() + 255) // 256 * 256
+        out.append(lbrb.lb_rb_adjoint(sim.ctx, T, K, at, n, a, 2, sum(len(b[0]) for b in bodies)))
+        sim.close()
+    tol = 1e-12 if precision == "f64" else 1e-6
+    for x, y in zip(*out):
+        x, y = np.asarray(x), np.asarray(y)
+        assert np.isfinite(x).all() and np.isfinite(y).all()
+        assert np.abs(x - y).max() <= tol * np.abs(x).max()
