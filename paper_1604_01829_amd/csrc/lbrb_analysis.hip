@@ -1012,9 +1012,11 @@ int lb_traj_lab_frame(const double* traj, int32_t n_frames, int32_t n_bodies, do
                         void* stream)
 {
     if (!frames_ok(traj, n_frames, n_bodies) || !out) return LB_ERR_ARG;
-    for (int32_t b = 0; b < n_bodies; b += 65535)   // (bodies along the grid's second dimension)
-        hipLaunchKernelGGL(lab_kernel, dim3((n_frames + kBlock - 1) / kBlock, std::min(n_bodies - b, 65535)),
-                           dim3(kBlock), 0, (hipStream_t)stream, traj, n_frames, n_bodies, b, out);
+    const dim3 block(kBlock);
+    const unsigned blocks = (unsigned)(((int64_t)n_frames + kBlock - 1) / kBlock);
+    for (int64_t b = 0; b < n_bodies; b += 65535)   // (bodies along the grid's second dimension)
+        hipLaunchKernelGGL(lab_kernel, dim3(blocks, (unsigned)std::min<int64_t>(n_bodies - b, 65535)), block,
+                           0, (hipStream_t)stream, traj, n_frames, n_bodies, (int)b, out);
     return launched();
 }
 
