@@ -257,7 +257,8 @@ struct AdjArgs {
     StepArgs<Real> a;
     const Real* lam_next;       // adjoint of the pre-collision populations of the next step
     Real* lam_cur;              // adjoint of the pre-collision populations of this step
-    Real* lamF;                 // adjoint of the node force density, [axis][node]
+    Real* lamF;                 // adjoint of the node force density, [axis][node], at the nodes
+                                // that the coupling of the step reached
     const Bead* beads;
     const BeadRec* recs;        // bead records (fixed bodies: the same for every step)
     const double* bead_force;   // bead forces of this step (lab frame)
@@ -308,7 +309,8 @@ void launch_adjoint_wca(const BodyArgs& ba, int par, const double* weights, cons
 void launch_records_from_poses(const Body* bodies, int par, const Bead* beads, BeadRec* recs,
                                int n_beads, hipStream_t s);
 
-// node pass: transposed streaming + collision VJP (writes lam_cur, lamF, consumes the force)
+// node pass: transposed streaming + collision VJP (writes lam_cur, and lamF at the nodes whose spread
+// force is flagged, consumes the force)
 template <typename Real>
 void launch_adjoint_step(const AdjArgs<Real>& A, bool masked, hipStream_t s);
 // bead pass: transpose of spreading, friction and interpolation, and of the velocity
