@@ -50,7 +50,11 @@ constexpr int kShellsPerLaunch = 64;
 constexpr int kNbSlots = kMaxBeads * 24;        // list entries per shell (96 KB of LDS)
 constexpr int kNbMax = 128;                     // list capacity per bead at most
 constexpr int kSplitMax = 640;                  // beads up to which closest points get their own waves
-constexpr double kSkin = 0.25;                  // list radius: the WCA cut plus kSkin
+// List radius: the WCA cut plus the skin, which does not touch the results.  A rebuild takes all pairs, so
+// shells of two beads a thread, where it is dear, keep longer lists.  Skin 0.25 / 0.4, from a separated
+// start: 2048 beads 300 steps 9.9 / 8.7 ms, 3000 steps 51.4 / 51.2; 1200 beads 5.4 / 4.8 and 29.8 /
+// 30.3; 700 beads 3.1 / 2.9 and 18.6 / 19.8.
+constexpr double kSkin = 0.25, kSkinLarge = 0.4;
 
 struct Shell {
     double axes[3];
@@ -201,8 +205,9 @@ __global__ __launch_bounds__(kBlock) void relax_kernel(const ShellBatch B, doubl
         amax = fmax(amax, a[k]);
     }
     const int cap = min(kNbMax, kNbSlots / 2 / max(n, 1) * 2);   // list entries per bead, even
-    const double rl = sqrt(p.rc2) + kSkin, rl2 = rl * rl;
-    const double move2 = 0.25 * kSkin * kSkin;       // (skin / 2)^2
+    const double skin = n <= kBlock ? kSkin : kSkinLarge;
+    const double rl = sqrt(p.rc2) + skin, rl2 = rl * rl;
+    const double move2 = 0.25 * skin * skin;         // (skin / 2)^2
     // up to kSplitMax beads: the first nf threads (whole waves) take the pair forces and the motion,
     // the others the closest points (at least 384 threads, so at most kPer each), left in the unused
     // second half of X
