@@ -147,6 +147,7 @@ struct ReplicaHost {
     int group = 0;            // 0 = dense tiles, 1 = masked tiles
     int64_t n_holes = 0;      // boundary nodes stored inside row spans (lbrb_walls.h)
     std::vector<uint8_t> hole_tiles;   // per tile: 1 if it holds one (empty: no holes)
+    std::vector<int32_t> tile_links;   // per tile: moving-wall links (empty: none)
     int32_t tile0 = 0, n_tiles = 0;
     std::vector<int32_t> bodies;
     std::vector<uint8_t> mask;      // boundary mask as set (wall ids), empty = all fluid
@@ -551,7 +552,7 @@ void rebuild_tiles(lb_ctx* c)
     }
 }
 
-int upload_tables(lb_ctx* c)
+int upload_tiles(lb_ctx* c)
 {
     // the tiles that hold holes, for the mirror launch
     c->hole_tiles.clear();
@@ -562,6 +563,17 @@ int upload_tables(lb_ctx* c)
         HIP_TRY(c, hipMemcpyAsync(c->d_hole_tiles, c->hole_tiles.data(),
                                   sizeof(NodeTile) * c->hole_tiles.size(), hipMemcpyHostToDevice,
                                   c->stream));
+    for (int g = 0; g < 2; ++g)
+        if (!c->tiles[g].empty())
+            HIP_TRY(c, hipMemcpyAsync(c->d_tiles[g], c->tiles[g].data(),
+                                      sizeof(NodeTile) * c->tiles[g].size(), hipMemcpyHostToDevice,
+                                      c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    return LB_OK;
+}
+
+int upload_tables(lb_ctx* c)
+{
     HIP_TRY(c, hipMemcpyAsync(c->d_reps, c->reps.data(), sizeof(ReplicaDesc) * c->n_rep,
                               hipMemcpyHostToDevice, c->stream));
     if (!c->rows.empty())
@@ -570,13 +582,7 @@ int upload_tables(lb_ctx* c)
     if (!c->rowinfo.empty())
         HIP_TRY(c, hipMemcpyAsync(c->d_rowinfo, c->rowinfo.data(), sizeof(RowDesc) * c->rowinfo.size(),
                                   hipMemcpyHostToDevice, c->stream));
-    for (int g = 0; g < 2; ++g)
-        if (!c->tiles[g].empty())
-            HIP_TRY(c, hipMemcpyAsync(c->d_tiles[g], c->tiles[g].data(),
-                                      sizeof(NodeTile) * c->tiles[g].size(), hipMemcpyHostToDevice,
-                                      c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    return LB_OK;
+    return upload_tiles(c);   // and waits for all of them
 }
 
 // equilibrium of (rho0, u0) in the current buffer for the tiles of one replica (or all)
@@ -634,8 +640,15 @@ int64_t links_without(const lb_ctx* c, int32_t replica)
     return n;
 }
 
-// the replicas' links, concatenated in replica order, and each tile's range of them (the links
-// of a replica are sorted by slot, so by tile)
+// a replica's links, with the number of each of its tiles (they are sorted by slot, so by tile)
+void set_links(ReplicaHost& H, const ReplicaDesc& R, std::vector<WallLink>& links)
+{
+    H.links.swap(links);
+    H.tile_links.assign(H.links.empty() ? 0 : (size_t)(R.n_fluid + kNodeBlock - 1) / kNodeBlock, 0);
+    for (const WallLink& L : H.links) ++H.tile_links[(L.g - R.base) / kNodeBlock];
+}
+
+// the replicas' links, concatenated in replica order, and each tile's range of them
 std::vector<WallLink> collect_links(lb_ctx* c)
 {
     std::vector<WallLink> all;
@@ -644,13 +657,11 @@ std::vector<WallLink> collect_links(lb_ctx* c)
         H.link0 = (int64_t)all.size();
         all.insert(all.end(), H.links.begin(), H.links.end());
         NodeTile* T = c->tiles[H.group].data() + H.tile0;
-        int64_t k = 0;
-        const int64_t n = (int64_t)H.links.size();
+        int64_t link0 = H.link0;
         for (int32_t t = 0; t < H.n_tiles; ++t) {
-            T[t].link0 = H.link0 + k;
-            const int64_t k0 = k;
-            while (k < n && (H.links[k].g >> kPopBlockLog) == T[t].gt) ++k;
-            T[t].n_links = (int32_t)(k - k0);
+            T[t].link0 = link0;
+            T[t].n_links = H.tile_links.empty() ? 0 : H.tile_links[t];
+            link0 += T[t].n_links;
         }
     }
     c->n_links = (int64_t)all.size();
@@ -1443,7 +1454,7 @@ int lb_set_boundary_mask(lb_ctx* c, int32_t replica, const uint8_t* mask)
     if (n_holes > 0)
         for (size_t k = 0; k < m.holes.size(); ++k)
             if (m.holes[k]) H.hole_tiles[k / kNodeBlock] = 1;
-    H.links.swap(links);
+    set_links(H, R, links);
     destroy_graphs(c);
     rebuild_tiles(c);
     const std::vector<WallLink> all_links = collect_links(c);
@@ -1482,10 +1493,10 @@ int lb_set_wall_velocity(lb_ctx* c, int32_t replica, int32_t wall, const double 
     if (links_without(c, replica) + (int64_t)links.size() > c->plan.link_cap)
         return fail(c, LB_ERR_CAPACITY, "moving-wall links exceed max_wall_links");
     H.uwall.swap(uw);
-    H.links.swap(links);
+    set_links(H, R, links);
     destroy_graphs(c);
     const std::vector<WallLink> all_links = collect_links(c);
-    int rc = upload_tables(c);   // the tiles' link ranges
+    int rc = upload_tiles(c);   // their link ranges
     if (rc == LB_OK) rc = upload_links(c, all_links);
     if (rc != LB_OK) return rc;
     return init_fluid(c, replica);
