@@ -938,16 +938,19 @@ template <class S>
 int64_t lag_blocks(int32_t n_lags) { return ((int64_t)n_lags + S::lags - 1) / S::lags; }
 
 // The MSD kernels' duration in us, for the choice between them: what one workgroup takes (start +
-// per_frame * frames: the latency of its chain) and what `blocks` of them cost the full GPU,
-// together as the root of the sum of squares.  Fitted to measured times (1 to 1024 bodies, 16 to
-// 8192 frames, 4 to 8191 lags; 1, 3 and 6 components), which it meets to 10 - 16 % r.m.s.
+// per_frame * frames: the latency of its chain) or what `blocks` of them cost the full GPU, whichever
+// is more, with a smooth passage (the fourth powers).  Fitted to measured times (1 to 1024 bodies, 16 to
+// 50,000 frames, 4 to 8191 lags; 1, 3 and 6 components), which it meets to 10 - 17 % r.m.s.; the
+// kernel chosen takes 1 % more than the fastest in the mean, at most 1.4 times it.
 struct MsdCost {
     double start, per_frame;               // of one workgroup alone, us
     double block_start, block_per_frame;   // of one among many, us
 
     double us(double frames, int64_t blocks) const
     {
-        return std::hypot(start + per_frame * frames, blocks * (block_start + block_per_frame * frames));
+        const double one = start + per_frame * frames;
+        const double all = blocks * (block_start + block_per_frame * frames);
+        return std::sqrt(std::hypot(one * one, all * all));
     }
 };
 
@@ -1050,9 +1053,9 @@ int lb_traj_msd(const double* series, int32_t n_frames, int32_t n_bodies, int32_
     const int64_t wide_blocks = lag_blocks<WideMsd>(n_lags) * n_bodies * k;
     // (the short kernel reads all components together; near the line it goes first, as the estimates
     // of the tiles are low for one component)
-    switch (fastest(0.9 * MsdCost{3.7, 0.0060, 0.0039, 1.0e-5}.us((double)n_frames * k, short_blocks),
-                    MsdCost{10.6, 0.0003, 0.037, 1.6e-6}.us(n_frames, narrow_blocks),
-                    MsdCost{9.9, 0.0032, 0.0104, 7.3e-6}.us(n_frames, wide_blocks))) {
+    switch (fastest(0.9 * MsdCost{3.65, 0.0063, 0.0046, 1.1e-5}.us((double)n_frames * k, short_blocks),
+                    MsdCost{10.7, 0.0007, 0.0365, 3.3e-6}.us(n_frames, narrow_blocks),
+                    MsdCost{10.1, 0.0033, 0.0105, 9.4e-6}.us(n_frames, wide_blocks))) {
     case MsdShape::Short: {
         const dim3 grid((unsigned)lag_blocks<ShortMsd>(n_lags), n_bodies);
         switch (k) {
@@ -1087,9 +1090,9 @@ int lb_traj_rotation_msd(const double* traj, int32_t n_frames, int32_t n_bodies,
     const int64_t short_blocks = lag_blocks<ShortMsd>(n_lags) * n_bodies;
     const int64_t narrow_blocks = lag_blocks<NarrowAngles>(n_lags) * n_bodies;
     const int64_t wide_blocks = lag_blocks<WideAngles>(n_lags) * n_bodies;
-    switch (fastest(MsdCost{5.5, 0.065, 0.005, 1.5e-4}.us(n_frames, short_blocks),
-                    MsdCost{11.7, 0.0117, 0.026, 2.7e-5}.us(n_frames, narrow_blocks),
-                    MsdCost{11.1, 0.044, 0.040, 1.65e-4}.us(n_frames, wide_blocks))) {
+    switch (fastest(MsdCost{5.5, 0.065, 0.0059, 1.64e-4}.us(n_frames, short_blocks),
+                    MsdCost{12.2, 0.0115, 0.027, 3.0e-5}.us(n_frames, narrow_blocks),
+                    MsdCost{11.9, 0.0427, 0.042, 1.76e-4}.us(n_frames, wide_blocks))) {
     case MsdShape::Short:
         hipLaunchKernelGGL(short_rotation_kernel, dim3(lag_blocks<ShortMsd>(n_lags), n_bodies),
                            dim3(kBlock), 0, s, traj, n_frames, n_bodies, ref_body, n_lags, out);
