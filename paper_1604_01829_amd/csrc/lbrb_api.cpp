@@ -1138,7 +1138,7 @@ int run_adjoint(lb_ctx* c, int32_t T, int32_t K, char* ws, const AdjPlan& ap)
 
 // ------------------------------------------------------------------ autotuner
 // The node update's launch settings -- node tiles per workgroup, a cap on the workgroups
-// resident per CU (by dynamic LDS), ordinary or non-temporal population stores -- are timed on
+// resident per CU (by dynamic LDS), cached or non-temporal population stores -- are timed on
 // the context's own node kernel over its own tiles: every tile group, the kernel the steps
 // launch (with the force path when the context has beads) but without body finishing, pulling
 // from the current buffer and writing the other one, which the next step overwrites whole.  With
