@@ -14,7 +14,7 @@
 //
 // Series are stored body-major, series[body][frame][k], so the MSD kernels read contiguous
 // frames.  Every sum runs in a fixed order (thread-strided loops, shuffle + LDS trees) and does
-// not depend on timing, but for the last bits of the binned sums of at most 8 bins.
+// not depend on timing, but for the last bits of the sums of more than two bodies in at most 8 bins.
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
